@@ -114,7 +114,11 @@ typedef struct {
  *   check_every  iterations between host reads of the device convergence flag (0: 32);
  *                launches after convergence return at once, so the count is exact
  *   graph        nonzero: each block of check_every iterations is captured once into a
- *                hipGraph and replayed; zero: plain launches
+ *                hipGraph and replayed; zero: plain launches.  A system whose vectors fit the
+ *                registers and LDS of the chip (about 1.3 million condition-DOFs; Neumann order
+ *                1 or Jacobi, GAP_ITERATION_STRIPS) runs its iterations inside one cooperative
+ *                launch instead, which the host reads when it ends (graph nonzero), or in one
+ *                such launch per check_every iterations (graph zero, check_every >= 4)
  *   iteration    GAP_ITERATION_TWO_LAUNCH: Table 1 as printed, two launches per iteration
  *                (u and u^T A u; then alpha and the updates).  GAP_ITERATION_ONE_LAUNCH:
  *                one launch per iteration, with u^T A u = z^T A z + 2 beta z^T A u_prev +

@@ -16,6 +16,7 @@
 #include "gap_pcg.hpp"
 #include "gap_pcg1.hpp"
 #include "gap_pcgw.hpp"
+#include "gap_pcgp.hpp"
 #include "gap_adjoint.hpp"
 
 namespace {
@@ -336,6 +337,66 @@ hipError_t launch_strip(int Q, int pk, int M, bool sync, bool init, const PcgDev
     return hipLaunchKernel(fn, dim3(blocks), dim3(kStripThreads), args, 0, st);
 }
 
+// ---- resident kernel (gap_pcgp.hpp) ----------------------------------------------------
+// Iterations of one cooperative launch, after which the host reads the record: many, or check_every
+// where plain launches were asked for (at least kLoopMinBlock of them, below which a launch per
+// iteration of the strip kernel is faster: 512 x 256 x 9, check_every 1: 41 us against 50).
+constexpr int kLoopPasses = 8192;
+constexpr int kLoopMinBlock = 4;
+constexpr size_t kLoopStaticLds = 16384;             // the kernel's own LDS, rounded up
+
+// Tiling of a joint system for the resident kernel: at most one workgroup per CU in all, the
+// lowest tiles built that cover the grid so, since the march over a tile (0.1 us a row) is the
+// longest part of an iteration.  The exchange of 252 workgroups takes 0.6 us longer than that of 180,
+// so up to 16 rows a tiling of at most 200 is preferred (256 x 128 x 9: 5.46 us per iteration with 6
+// rows and 252 workgroups, 5.06 with 8 and 180).  Returns the rows, 0 if the system does not fit.
+int loop_plan(int nt, int nz, int n_cond, int cus, int lds_max, LoopDev& lp)
+{
+    int groups = 1;
+    strip_layout(nt, 1, 1, lp.strips, groups);
+    const int most = std::min(cus, kLoopSlotsAll);
+    auto fits = [&](int R, int slots) {
+        lp.chunks = (nz + R - 1) / R;
+        lp.slots = (lp.strips * lp.chunks + kLoopWaves - 1) / kLoopWaves;
+        return lp.slots * n_cond <= slots && kLoopWaves * loop_tile_bytes(R) + kLoopStaticLds <= (size_t)lds_max;
+    };
+#define GAP_LOOP_CASE(r_) if (r_ <= 16 && fits(r_, std::min(most, 200))) return r_;
+    GAP_LOOP_ROWS(GAP_LOOP_CASE)
+#undef GAP_LOOP_CASE
+#define GAP_LOOP_CASE(r_) if (fits(r_, most)) return r_;
+    GAP_LOOP_ROWS(GAP_LOOP_CASE)
+#undef GAP_LOOP_CASE
+    return 0;
+}
+
+// Whether a solve may take the resident kernel's order of summation.  A joint recurrence over the
+// conditions is insensitive to it (1e-15 in p at any tolerance).  A recurrence of one condition
+// is not: where its Ritz values have converged, a change in the last bit of a sum grows until
+// about the residual 1e-6 and shrinks with the residual after it (150 x 61 textured, between any two
+// of the kernels: 3e-9 in p at residual 2e-7, 3e-10 at 9e-9).  A single condition takes this kernel
+// only if it goes on to kLoopTight; several with a recurrence each (forward differences would multiply
+// what is left by 1 / delta) do not.
+constexpr double kLoopTight = 1e-9;
+bool loop_order_ok(const PcgDev& a)
+{
+    if (a.n_cond > 1) return !a.per_cond;
+    return (a.async ? a.eps_c[0] : a.eps) <= kLoopTight;
+}
+
+// Device memory of the resident kernel's exchange: state, abort word, words (on cache lines of their own).
+constexpr size_t kScalarsBytes = (sizeof(PcgScalars) + 255) / 256 * 256;
+constexpr size_t kLoopStateBytes = (2 * sizeof(LoopState) + sizeof(int) + 255) / 256 * 256;
+constexpr size_t kLoopBytes = kLoopStateBytes + kLoopWords * sizeof(loop_word);
+
+const void* loop_fn(int pk, int rows)
+{
+#define GAP_LOOP_CASE(r_) \
+    if (rows == r_) return pk == 2 ? (const void*)k_pcg_p<2, r_> : pk == 0 ? (const void*)k_pcg_p<0, r_> : nullptr;
+    GAP_LOOP_ROWS(GAP_LOOP_CASE)
+#undef GAP_LOOP_CASE
+    return nullptr;
+}
+
 template <int NT, int Q>
 const void* pcg_fn(int which)
 {
@@ -468,6 +529,12 @@ struct gap_grid_s {
     };
     std::vector<Sched> scheds;
     PcgDev *req_dev = nullptr, *req_host = nullptr;          // the request record of this handle's launches
+    // resident kernel, in the allocation of sc: its state [2], the abort word and the exchanged words
+    LoopState* loop_state = nullptr;
+    int* loop_host = nullptr;                                // copy of the abort word, in that of sc_host
+    unsigned loop_base = 0;                                  // passes numbered so far
+    bool loop_clear = true;                                  // the words hold unknown passes
+    double* loop_p0 = nullptr;                               // warm start: the initial guess, should a launch give up
     double *adj_rhs = nullptr, *adj_lam = nullptr;           // adjoint right-hand sides and solutions
     double *adj_part = nullptr;                              // sensitivity partials
     double *step_buf = nullptr;                              // general iteration: F (9 x 4) and J (4 x 8)
@@ -526,7 +593,7 @@ namespace {
 void release(gap_grid_t g)
 {
     double* bufs[] = {g->trig, g->tex, g->kx, g->kz, g->kxz, g->minv, g->S, g->r0, g->r1, g->z, g->z1, g->partial,
-                      g->pcg_part, g->adj_rhs, g->adj_lam, g->adj_part, g->step_buf, g->hist};
+                      g->pcg_part, g->adj_rhs, g->adj_lam, g->adj_part, g->step_buf, g->hist, g->loop_p0};
     for (double* b : bufs)
         if (b) (void)hipFree(b);
     for (auto& gr : g->graphs)
@@ -637,6 +704,107 @@ void fill_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o)
     a.precond = o->precond;
 }
 
+// The resident kernel on a schedule of `blocks` workgroups: a cooperative launch per block of
+// iterations, or, with kernel timing, one launch per iteration of the same kernel.  A cooperative launch that the device refuses, or that gave up waiting for its
+// other workgroups, is replaced by the second form from the start of the solve.
+gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev lp, int rows, const int* work, int blocks,
+                    hipStream_t st)
+{
+    const int check_every = o->check_every ? o->check_every : 32;
+    const size_t p_bytes = (size_t)a.n_cond * g->n * sizeof(double);
+    lp.state = g->loop_state;
+    lp.abort_word = (int*)(g->loop_state + 2);
+    lp.words = (loop_word*)((char*)g->loop_state + kLoopStateBytes);
+    const void* fn = loop_fn(o->precond, rows);
+    const PcgDev* reqs = g->req_dev;
+    const size_t lds = kLoopWaves * loop_tile_bytes(rows);
+    int par = 0;
+    auto launch = [&](int init, int n_pass, bool coop) -> hipError_t {
+        void* args[] = {(void*)&reqs, (void*)&lp, (void*)&work, (void*)&init, (void*)&n_pass, (void*)&par,
+                        (void*)&g->loop_base};
+        const hipError_t e = coop ? hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(kLoopThreads), args, (unsigned)lds, st)
+                                  : hipLaunchKernel(fn, dim3(blocks), dim3(kLoopThreads), args, lds, st);
+        if (e == hipSuccess) par ^= 1;
+        return e;
+    };
+    auto start = [&]() -> gap_status {               // number the passes of a solve from here
+        if (g->loop_clear || g->loop_base > 0x60000000u) {
+            HIPCHK(hipMemsetAsync(g->loop_state, 0, kLoopBytes, st));
+            g->loop_base = 0;
+        }
+        g->loop_clear = true;                        // until the solve has ended in order
+        par = 0;
+        return GAP_OK;
+    };
+    auto finish = [&]() {                            // passes the solve has numbered at most
+        g->loop_base += (unsigned)g->sc_host->iterations + 4u;
+        g->loop_clear = false;
+    };
+    gap_status ss = start();
+    if (ss != GAP_OK) return ss;
+    if (!g->timing) {
+        const int passes = o->graph != 0 ? kLoopPasses : check_every;
+        if (a.warm) {
+            if (!g->loop_p0) {
+                gap_status s1 = dmalloc(&g->loop_p0, (size_t)g->max_cond * g->n);
+                if (s1 != GAP_OK) return s1;
+            }
+            HIPCHK(hipMemcpyAsync(g->loop_p0, a.p, p_bytes, hipMemcpyDeviceToDevice, st));
+        }
+        hipError_t e = launch(1, passes, true);
+        bool gave_up = e != hipSuccess;
+        if (gave_up) (void)hipGetLastError();
+        const long max_blocks = o->max_iter / passes + 2;
+        for (long blk = 0; blk < max_blocks && !gave_up; ++blk) {
+            if (blk) {
+                e = launch(0, passes, true);
+                if (e != hipSuccess) return fail(GAP_EDEVICE, "launch of the resident kernel: %s", hipGetErrorString(e));
+            }
+            HIPCHK(hipMemcpyAsync(g->sc_host, g->sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipMemcpyAsync(g->loop_host, lp.abort_word, sizeof(int), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            gave_up = *g->loop_host != 0;
+            if (!gave_up && g->sc_host->done) {
+                finish();
+                return GAP_OK;
+            }
+        }
+        if (!gave_up) return GAP_OK;
+        if (a.warm) HIPCHK(hipMemcpyAsync(a.p, g->loop_p0, p_bytes, hipMemcpyDeviceToDevice, st));
+        ss = start();
+        if (ss != GAP_OK) return ss;
+    }
+    hipError_t le = launch(1, 0, false);
+    if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of the initial residual kernel: %s", hipGetErrorString(le));
+    const long max_blocks = o->max_iter / check_every + 2;
+    long enqueued = 0;
+    for (long blk = 0; blk < max_blocks; ++blk) {
+        const long remaining = (long)o->max_iter - enqueued;
+        const bool last = remaining < check_every;
+        const int iters = last ? (int)remaining : check_every;
+        if (g->timing) {
+            gap_status ts = timing_reserve(g, 2 * iters + 1);
+            if (ts != GAP_OK) return ts;
+        }
+        for (int it = 0; it < iters + (last ? 1 : 0); ++it) {   // last: and the closing launch
+            timing_mark(g, GAP_KERNEL_PCG_STRIPS, true, st);
+            le = launch(0, 1, false);
+            timing_mark(g, GAP_KERNEL_PCG_STRIPS, false, st);
+            if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of a PCG iteration: %s", hipGetErrorString(le));
+        }
+        enqueued += iters;
+        HIPCHK(hipMemcpyAsync(g->sc_host, g->sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (g->timing) {
+            gap_status ts = timing_collect(g);
+            if (ts != GAP_OK) return ts;
+        }
+        if (g->sc_host->done) break;
+    }
+    if (g->sc_host->done) finish();
+    return GAP_OK;
+}
+
 gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_t st)
 {
     const int check_every = o->check_every ? o->check_every : 32;
@@ -646,7 +814,25 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     const int kernel_one = strip ? GAP_KERNEL_PCG_STRIPS : GAP_KERNEL_PCG_ONE;
     fill_pcg(g, a, o);
     a.n_strips = a.strip_groups = 1;
-    if (strip) {
+    // Systems whose vectors fit the registers and LDS of the chip run the resident kernel; it needs
+    // Neumann order 1 or Jacobi.  A caller that reads the record after every few plain launches
+    // keeps a launch per iteration: starting and saving the tiles costs a resident launch 20-35 us.
+    LoopDev lp{};
+    const bool blocks_ok = o->graph != 0 || check_every >= kLoopMinBlock;
+    const int loop_rows = strip && o->neumann == 1 && blocks_ok && loop_order_ok(a) ? loop_plan(g->nt, g->nz, a.n_cond, g->cus, g->lds_max, lp) : 0;
+    const bool loop = loop_rows > 0 && loop_fn(o->precond, loop_rows);
+    if (loop) {
+        const hipError_t fe = hipFuncSetAttribute(loop_fn(o->precond, loop_rows), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  (int)(kLoopWaves * loop_tile_bytes(loop_rows)));
+        if (fe != hipSuccess) return fail(GAP_EDEVICE, "preparing the resident kernel: %s", hipGetErrorString(fe));
+        if (a.n_cond == 1 && a.async) {              // one condition: its own stopping test is the joint one
+            a.eps = a.eps_c[0];
+            a.async = 0;
+        }
+        if (a.n_cond == 1) a.per_cond = 0;
+        a.chunks_b = a.chunks_a = lp.slots;
+        a.rows_b = a.rows_a = loop_rows;
+    } else if (strip) {
         const int M = o->neumann, Q = strip_q(g->shape_w.Q, M);
         if (!g->occ_wm[Q][M]) {
             int occ = 1;
@@ -675,7 +861,7 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     // schedule tables for this (iteration kind, kernel shapes, n_cond, chunk counts, operator
     // map); graphs are cached by table, so the shapes belong to the key
     std::vector<int> key = {o->iteration, one ? 0 : g->shape_a.NT, one ? 0 : g->shape_a.Q, sh_b.NT, sh_b.Q, sh_b.pk,
-                            sh_b.M, sh_b.sync, a.n_cond, a.chunks_a, a.chunks_b};
+                            sh_b.M, sh_b.sync, loop ? 1 : 0, a.n_cond, a.chunks_a, a.chunks_b};
     for (int c = 0; c < a.n_cond; ++c) key.push_back(a.op[c]);
     gap_grid_s::Sched* sch = nullptr;
     for (auto& e : g->scheds)
@@ -683,7 +869,7 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     if (!sch) {
         std::vector<std::vector<int>> ga, gb;
         if (!one) pcg_groups(0, a.chunks_a, a.n_cond, a.op, ga);
-        pcg_groups(0, a.chunks_b, a.n_cond, a.op, gb, strip ? a.strip_groups : 1);
+        pcg_groups(0, a.chunks_b, a.n_cond, a.op, gb, strip && !loop ? a.strip_groups : 1);
         const std::vector<int> ta = pcg_schedule(ga), tb = pcg_schedule(gb);
         gap_grid_s::Sched e;
         e.key = key;
@@ -715,6 +901,7 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     *g->req_host = a;
     HIPCHK(hipMemcpyAsync(g->req_dev, g->req_host, sizeof(PcgDev), hipMemcpyHostToDevice, st));
 
+    if (loop) return run_loop(g, a, o, lp, loop_rows, work_b, sch->blocks_b, st);
     hipError_t le = launch_pcg(sh_b, strip ? kPcgStripInit : (one ? kPcgOneInit : kPcgInit), g->nt, g->req_dev, work_b,
                                sch->blocks_b, st);
     if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of the initial residual kernel: %s", hipGetErrorString(le));
@@ -1123,16 +1310,19 @@ gap_status create_gap_grid(const gap_geom* geom, const gap_dimples* dimples, int
     ALLOC(g->partial, 10 * max_chunks);
     ALLOC(g->pcg_part, 15 * max_pcg);
 #undef ALLOC
-    if (hipMalloc((void**)&g->sc, sizeof(PcgScalars)) != hipSuccess) {
+    if (hipMalloc((void**)&g->sc, kScalarsBytes + kLoopBytes) != hipSuccess) {
         g->sc = nullptr;
         release(g);
         return fail(GAP_ENOMEM, "hipMalloc of the scalar block failed");
     }
-    if (hipHostMalloc((void**)&g->sc_host, sizeof(PcgScalars), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&g->sc_host, kScalarsBytes + sizeof(int), hipHostMallocDefault) != hipSuccess) {
         g->sc_host = nullptr;
         release(g);
         return fail(GAP_ENOMEM, "hipHostMalloc of the scalar block failed");
     }
+
+    g->loop_state = (LoopState*)((char*)g->sc + kScalarsBytes);
+    g->loop_host = (int*)((char*)g->sc_host + kScalarsBytes);
 
     std::vector<double> trig(4 * nt);
     for (size_t i = 0; i < nt; ++i) {
@@ -2189,7 +2379,7 @@ gap_status gap_grid_bytes(const gap_geom* geom, int32_t max_cond, int64_t* bytes
     strip_layout((int)nt, 1, kStripMaxNeumann, strips1, groups1);
     d += 15 * (int64_t)max_cond * std::max<int64_t>(nz, groups1);   // PCG partials
     d += (int64_t)max_cond * n;                              // the caller's pressure field
-    *bytes = d * (int64_t)sizeof(double) + 4096;
+    *bytes = d * (int64_t)sizeof(double) + 4096 + (int64_t)kLoopBytes;
     return GAP_OK;
 }
 
