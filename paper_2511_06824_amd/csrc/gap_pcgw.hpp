@@ -108,6 +108,17 @@ __device__ __forceinline__ double read_lane(double x, int l)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// First ring column that strip i of n_strips owns, floor(i n_theta / n_strips): in 32 bits wherever
+// the products fit (a 64-bit division takes some hundred instructions).
+__device__ __forceinline__ int strip_column(int i, int nt, int n_strips)
+{
+    if (n_strips < 65536) {
+        const unsigned whole = (unsigned)nt / (unsigned)n_strips, rest = (unsigned)nt - whole * (unsigned)n_strips;
+        return (int)((unsigned)i * whole + (unsigned)i * rest / (unsigned)n_strips);
+    }
+    return (int)(((long long)i * nt) / n_strips);
+}
+
 // Value of the strip column one to the west (m - 1) of each lane's column m = lane + 64 q:
 // lane l - 1 of the same block, lane 63 of block q - 1 for lane 0 (0 at the strip's west end).
 template <int Q>
@@ -125,61 +136,122 @@ __device__ __forceinline__ void east_of(const double (&x)[Q], double (&e)[Q])
     for (int q = 0; q < Q; ++q) e[q] = q < Q - 1 ? dpp_shift<0x130>(x[q], read_lane(x[q + 1], 0)) : dpp_shift0<0x130>(x[q]);
 }
 
-// Per-condition sums of NQ partial arrays of `chunks` slots each, in the order of cond_sums
-// (wave w takes conditions w, w + NW, ...; lane l adds slots l, l + 64, ... to a zero start;
-// then the same shuffle tree), so the sums are the same to the bit.  The loads of a round of
-// 64 slots go out for all of a wave's conditions and arrays together: one memory latency per
-// round instead of one per condition and array.  Threads 0 .. n_cond - 1 also copy gsrc[t]
-// to gout[t] on the way.  Results in out[q][c] and gout, valid after the trailing barrier.
-template <int NT, int NQ>
-__device__ __forceinline__ void strip_cond_sums(int n_cond, int chunks, const double* const (&src)[NQ],
-                                                double (*out)[GAP_MAXC], const double* gsrc, double* gout)
+// Halving steps of a sum over the 64 lanes.  After halve32, lanes 0-31 hold a's sums over lanes
+// that differ by 32 and lanes 32-63 b's; after halve16, even rows of 16 lanes hold a's sums over
+// lanes that differ by 16 and odd rows b's.  One instruction per 32-bit word exchanges the halves.
+__device__ __forceinline__ double halve(unsigned a0, unsigned a1, unsigned b0, unsigned b1)
 {
-    constexpr int NW = NT / 64;
-    constexpr int R = (GAP_MAXC + NW - 1) / NW;     // conditions per wavefront at most
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const bool gcopy = (int)threadIdx.x < n_cond;
-    double g = 0.0;
-    if (gcopy) g = gsrc[threadIdx.x];
-    double v[R][NQ];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) v[r][q] = 0.0;
-    for (int k0 = 0; k0 < chunks; k0 += 64) {
-        const int k = k0 + lane;
-        double x[R][NQ];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool ok = w + r * NW < n_cond && k < chunks;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) x[r][q] = ok ? src[q][(w + r * NW) * chunks + k] : 0.0;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool ok = w + r * NW < n_cond && k < chunks;
-#pragma unroll
-            for (int q = 0; q < NQ; ++q)
-                if (ok) v[r][q] += x[r][q];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v[r][q] += __shfl_xor(v[r][q], off, 64);
-    if (lane == 0) {
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (w + r * NW < n_cond) {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) out[q][w + r * NW] = v[r][q];
-            }
-    }
-    if (gcopy) gout[threadIdx.x] = g;
-    __syncthreads();
+    return __hiloint2double((int)a1, (int)a0) + __hiloint2double((int)b1, (int)b0);
 }
+__device__ __forceinline__ double halve32(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return halve(lo[0], hi[0], lo[1], hi[1]);
+}
+__device__ __forceinline__ double halve16(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return halve(lo[0], hi[0], lo[1], hi[1]);
+}
+// The sum over the 16 lanes of a row, in every one of them: lanes that differ by 8, 4, 2, 1 (row_ror:8,
+// row_ror:4 on values that repeat after 8 lanes, quad_perm 2,3,0,1 and 1,0,3,2).
+__device__ __forceinline__ double row_sum(double x)
+{
+    x += dpp_shift0<0x128>(x);
+    x += dpp_shift0<0x124>(x);
+    x += dpp_shift0<0x4E>(x);
+    return x + dpp_shift0<0xB1>(x);
+}
+// Sums of 4 N values over the 64 lanes, in the order of a shuffle tree with offsets 32, 16, 8, 4, 2,
+// 1: value i + N (lane >> 4) of the N values i comes out in x[i].  Two halving steps leave N sums to
+// finish instead of 4 N, and no step goes through the LDS.
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&x)[4 * N])
+{
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) x[i] = halve32(x[i], x[i + 2 * N]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = row_sum(halve16(x[i], x[i + N]));
+}
+
+// The sums of an iteration's partial arrays, kStripParts + 1 per condition (value q of condition c in
+// out[c * kStride + q]), `chunks` slots each.  Wavefront w takes the conditions w, w + kStripWaves,
+// ...; lane l adds slots l, l + 64, ... to a zero start, then the 64 lanes are added in a fixed tree.
+// load() sends the loads of the first 64 kRounds slots of all of them out together, finish() adds
+// them up; the sums are valid after a barrier.
+//
+// Latency bound: every workgroup of a launch does this at its start, with no other work on the
+// chip to run meanwhile.  In cycles of the first wavefront (9 conditions of 1024 x 512, 85 slots
+// each): start of the kernel to the first row loads 5000, sums 13400, scalars of the iteration 7400
+// with a shuffle tree per array through the LDS, a serial loop over the conditions in every thread and
+// 64-bit divisions for the strip's columns; 10000, 2000 and 2800 with the sums' loads sent out before
+// the stop flag is looked at, halving steps in registers and one lane per condition.  Per iteration
+// 58.8 -> 50.9 us (1024 x 512, 9 conditions), 41.7 -> 33.0 us (its 5 adjoint systems), 69.7 -> 61.7 us
+// (800 x 760, 9), 216 -> 208 us (2048 x 1024, 9).
+struct StripSums {
+    static constexpr int kParts = kStripParts + 1, kStride = kParts + 1;
+    static constexpr int kConds = (GAP_MAXC + kStripWaves - 1) / kStripWaves;
+    static constexpr int kRounds = 3;
+    static constexpr int kValues = 4 * ((kConds * kParts + 3) / 4);
+    double x[kRounds][kConds * kParts];
+
+    __device__ __forceinline__ void load(const double* parts, const double* part_ss, size_t fs, int chunks, int n_cond,
+                                         int wave, int lane)
+    {
+#pragma unroll
+        for (int m = 0; m < kRounds; ++m) {
+#pragma unroll
+            for (int i = 0; i < kConds * kParts; ++i) x[m][i] = 0.0;
+            const unsigned k = lane + 64 * m;
+            if (k < (unsigned)chunks) {
+#pragma unroll
+                for (int i = 0; i < kConds; ++i) {
+                    const int c = wave + kStripWaves * i;
+                    if (c < n_cond) {
+#pragma unroll
+                        for (int q = 0; q < kParts; ++q)
+                            x[m][i * kParts + q] = as_global((q < kStripParts ? parts + q * fs : part_ss) + c * chunks)[k];
+                    }
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(const double* parts, const double* part_ss, size_t fs, int chunks, int n_cond,
+                                           int wave, int lane, double* out)
+    {
+        double v[kValues];
+        // a slot that does not exist adds +0 to a sum that is never -0
+#pragma unroll
+        for (int i = 0; i < kValues; ++i) {
+            v[i] = 0.0;
+            if (i < kConds * kParts) {
+#pragma unroll
+                for (int m = 0; m < kRounds; ++m) v[i] += x[m][i];
+            }
+        }
+        for (int k = lane + 64 * kRounds; k < chunks; k += 64) {
+#pragma unroll
+            for (int i = 0; i < kConds; ++i) {
+                const int c = wave + kStripWaves * i;
+                if (c < n_cond) {
+#pragma unroll
+                    for (int q = 0; q < kParts; ++q)
+                        v[i * kParts + q] += as_global((q < kStripParts ? parts + q * fs : part_ss) + c * chunks)[k];
+                }
+            }
+        }
+        wave_sums<kValues / 4>(v);
+        if ((lane & 15) == 0) {
+#pragma unroll
+            for (int i = 0; i < kValues / 4; ++i) {
+                const int k = i + kValues / 4 * (lane >> 4), r = k / kParts, c = wave + kStripWaves * r;
+                if (c < n_cond) out[c * kStride + (k - r * kParts)] = v[i];
+            }
+        }
+    }
+};
 
 // Runs the row steps of phases PH .. P - 1 (fn(s, phase) each), advancing s; false once s has
 // passed s_last.  Unrolled at compile time, so each step sees its phase as a constant.
@@ -205,28 +277,38 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
     const PcgDev& a = reqs[req];
     const int par = (launch_par ^ a.par_off) & 1;
     const bool writer = (c == 0 && kc == 0);    // publishes the request's device record
-    if (!INIT && a.sc->done_f[par]) {
-        if (writer && threadIdx.x == 0) a.sc->done_f[par ^ 1] = 1;
-        return;
-    }
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // the record's fields of this launch and the partial sums go out first, all of them together;
+    // the geometry of the strip is worked out while they are on their way
+    const int n_cond = a.n_cond, chunks = a.chunks_b;
     const size_t fs = (size_t)a.fstride;
-    const int slot = c * a.chunks_b + kc;
+    const double* rparts = a.fpart[par];
+    const double* rss = a.part_ss;
     double* wpart = a.fpart[INIT ? 0 : (par ^ 1)];
-    if (!INIT && a.async && !writer && !((a.sc->act_f[par] >> c) & 1)) {
-        if (t == 0)
-            for (int q = 0; q < kStripParts; ++q) wpart[q * fs + slot] = a.fpart[par][q * fs + slot];
-        return;
+    const int mine = min(lane, n_cond - 1);      // the condition whose scalars this lane forms
+    int done = 0, was = 0, j = -1;
+    double gam_prev = 0.0, alf_prev = 0.0, eps_mine = 0.0;
+    StripSums part;
+    if (!INIT) {
+        const GAP_AS1 PcgScalars* sc = as_global(a.sc);
+        done = sc->done_f[par];
+        was = sc->act_f[par];
+        j = sc->iter_f[par];
+        gam_prev = sc->gam[par][mine];
+        alf_prev = sc->alf[par][c];
+        eps_mine = as_global(a.eps_c)[mine];
+        part.load(rparts, rss, fs, chunks, n_cond, wave, lane);
     }
+    const int slot = c * chunks + kc;
     const int nt = a.nt, nz = a.nz;
-    const int rchunk = kc / a.strip_groups, grp = kc - rchunk * a.strip_groups;
+    const int rchunk = (int)((unsigned)kc / (unsigned)a.strip_groups), grp = kc - rchunk * a.strip_groups;
     const int j0 = rchunk * a.rows_b, j1 = min(j0 + a.rows_b, nz);
-    const int lane = t & 63;
     const int strip = grp * kStripWaves + (t >> 6);
     const bool has_strip = strip < a.n_strips;
     // owned ring columns [oc0, oc1); strip column m is ring column (oc0 - halo + m) mod nt
-    const int oc0 = (int)(((long long)strip * nt) / a.n_strips);
-    const int oc1 = (int)(((long long)(strip + 1) * nt) / a.n_strips);
+    const int oc0 = strip_column(strip, nt, a.n_strips);
+    const int oc1 = strip_column(strip + 1, nt, a.n_strips);
     int gcol[Q];
     bool ownc[Q];
 #pragma unroll
@@ -238,12 +320,13 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
         ownc[q] = has_strip && m >= strip_halo(M) && m < strip_halo(M) + (oc1 - oc0);
     }
 
-    const int j = INIT ? -1 : a.sc->iter_f[par];
     const size_t n = (size_t)nt * nz;
     const int pk = PK >= 0 ? PK : a.precond;  // 0 Jacobi, 1 ASSOR I, 2 ASSOR II
     const bool spmv = !INIT || a.warm;
     const bool has_prev = !INIT && j > 0;
-    const bool odd = !INIT && (j & 1);
+    // iteration j runs in launches of parity j: the buffers are known before j is
+    const int jp = INIT ? 1 : par;
+    const bool odd = !INIT && jp;
     const int op = a.op[c];
     const GAP_AS1 double* kx = as_global(a.kx + (size_t)op * n);
     const GAP_AS1 double* kz = as_global(a.kz + (size_t)op * (n + nt));
@@ -259,12 +342,12 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
     // of the same blocks), reads u_{j-1} of row s - M where it is needed, and reads kx and kz.
     constexpr bool kPairs = (M <= 2);
     constexpr int DU = kPairs ? M : 0;           // ring index of u_{j-1} of row s - M
-    const GAP_AS1 double* ruin = as_global(a.r[j & 1] + 2 * co);       // pair g at [2g], [2g + 1]
-    GAP_AS1 double* ruout = as_global(a.r[(j + 1) & 1] + 2 * co);
-    const GAP_AS1 double* rin = as_global((INIT ? a.S : a.r[j & 1]) + co);   // separate arrays
-    GAP_AS1 double* rout = as_global(a.r[(j + 1) & 1] + co);
-    const GAP_AS1 double* uin = as_global((INIT ? a.p : a.u[(j + 1) & 1]) + co);
-    GAP_AS1 double* uout = as_global(a.u[j & 1] + co);
+    const GAP_AS1 double* ruin = as_global(a.r[jp] + 2 * co);       // pair g at [2g], [2g + 1]
+    GAP_AS1 double* ruout = as_global(a.r[jp ^ 1] + 2 * co);
+    const GAP_AS1 double* rin = as_global((INIT ? a.S : a.r[jp]) + co);   // separate arrays
+    GAP_AS1 double* rout = as_global(a.r[jp ^ 1] + co);
+    const GAP_AS1 double* uin = as_global((INIT ? a.p : a.u[jp ^ 1]) + co);
+    GAP_AS1 double* uout = as_global(a.u[jp] + co);
     GAP_AS1 double* pp = as_global(a.p + co);
 
     // Row pipeline with Neumann order M (the lags grow with M): S1, S2 on row s; the second
@@ -350,6 +433,15 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
             }
         }
     };
+    if (!INIT && done) {
+        if (writer && t == 0) a.sc->done_f[par ^ 1] = 1;
+        return;
+    }
+    if (!INIT && a.async && !writer && !((was >> c) & 1)) {
+        if (t == 0)
+            for (int q = 0; q < kStripParts; ++q) wpart[q * fs + slot] = rparts[q * fs + slot];
+        return;
+    }
     // The loads of the first steps go out before the reduction of the scalars, whose latency
     // they overlap; they do not depend on alpha or beta.
     if (has_strip) {
@@ -366,84 +458,84 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
     // ---- scalars (as in the ring kernel) ------------------------------------------------
     double alpha = 1.0, beta = 0.0, a_prev = 0.0;
     if (!INIT) {
-        // the device record's fields are read before the reduction's barrier, so that their
-        // latency overlaps that of the partial sums; r.z of the previous launch goes through LDS
-        __shared__ double sums[kStripParts + 1][GAP_MAXC];
-        __shared__ double gprev[GAP_MAXC];
-        const unsigned was_active = (unsigned)a.sc->act_f[par];
-        const double alf_prev = odd ? a.sc->alf[par][c] : 0.0;
-        {
-            const double* rp = a.fpart[par];
-            const double* src[kStripParts + 1] = {rp, rp + fs, rp + 2 * fs, rp + 3 * fs, rp + 4 * fs, a.part_ss};
-            strip_cond_sums<kStripThreads, kStripParts + 1>(a.n_cond, a.chunks_b, src, sums, a.sc->gam[par], gprev);
+        __shared__ double sums[GAP_MAXC * StripSums::kStride];
+        part.finish(rparts, rss, fs, chunks, n_cond, wave, lane, sums);
+        if (t < n_cond) sums[t * StripSums::kStride + StripSums::kParts] = gam_prev;
+        __syncthreads();
+        // lane k forms the scalars of condition k
+        const bool on = lane < n_cond;
+        const unsigned was_active = (unsigned)was, all = (1u << n_cond) - 1;
+        const double* own_sums = sums + mine * StripSums::kStride;
+        const double rz_k = own_sums[0], rr_k = own_sums[1], zaz_k = own_sums[2], zau_k = own_sums[3],
+                     uau_k = own_sums[4], ss_k = own_sums[5];
+        unsigned active = all;
+        double rel_k = 0.0;
+        if (a.async || writer) rel_k = sqrt(rr_k / (ss_k > 0.0 ? ss_k : 1.0));
+        if (a.async) active = (unsigned)__ballot(on && ((was_active >> mine) & 1) && rel_k > eps_mine);
+        const bool act = (active >> lane) & (lane < 32);
+        // sums over the conditions in their order, one per lane: r.r, S.S, and of the active ones
+        // r.z and the previous r.z (a condition left out adds +0 to a sum that is never -0)
+        const double* col = sums + ((0x6051 >> (4 * (lane & 3))) & 7);
+        const unsigned in = lane & 2 ? active : all;
+        double tot = 0.0;
+#pragma unroll
+        for (int k = 0; k < GAP_MAXC; ++k) {
+            const double v = col[k * StripSums::kStride];
+            tot += (in >> k) & 1 ? v : 0.0;
         }
-        unsigned active = 0;
-        double rr = 0.0, ss = 0.0;
-        for (int k = 0; k < a.n_cond; ++k) {
-            const double sk = sums[5][k] > 0.0 ? sums[5][k] : 1.0;
-            const bool act = !a.async || (((was_active >> k) & 1) && sqrt(sums[1][k] / sk) > a.eps_c[k]);
-            if (act) active |= 1u << k;
-            rr += sums[1][k];
-            ss += sums[5][k];
-        }
+        const double rr = read_lane(tot, 0), ss = read_lane(tot, 1), dn = read_lane(tot, 2), dp = read_lane(tot, 3);
         const double rel = sqrt(rr / (ss > 0.0 ? ss : 1.0));
         const bool converged = a.async ? (active == 0) : (rel <= a.eps);
         bool bad = !finite_d(rel);
-        double alk[GAP_MAXC];
-        for (int k = 0; k < GAP_MAXC; ++k) alk[k] = 0.0;
+        // the scalars are formed whether or not the iteration goes on: no branch keeps them from
+        // overlapping the square root and the quotient of the test
+        double b_k = a.per_cond ? rz_k / gam_prev : dn / dp;
+        b_k = j > 0 ? b_k : 0.0;
+        double den_k = j > 0 ? zaz_k + 2.0 * b_k * zau_k + b_k * b_k * uau_k : zaz_k;
+        double num_k = rz_k;
+        if (!a.per_cond) {
+            den_k = act ? den_k : 0.0;
+            double uau = 0.0;
+#pragma unroll
+            for (int k = 0; k < GAP_MAXC; ++k) uau += read_lane(den_k, k);
+            den_k = uau;
+            num_k = dn;
+        }
+        double al_k = num_k / den_k;
         if (!converged && j < a.max_iter) {
-            auto den = [&](int k, double b) {
-                return j > 0 ? sums[2][k] + 2.0 * b * sums[3][k] + b * b * sums[4][k] : sums[2][k];
-            };
-            if (a.per_cond) {
-                for (int k = 0; k < a.n_cond; ++k) {
-                    if (!(active & (1u << k))) continue;
-                    const double bk = j > 0 ? sums[0][k] / gprev[k] : 0.0;
-                    alk[k] = sums[0][k] / den(k, bk);
-                    bad |= !finite_d(bk) || !finite_d(alk[k]);
-                }
-                beta = j > 0 ? sums[0][c] / gprev[c] : 0.0;
-                alpha = sums[0][c] / den(c, beta);
-            } else {
-                double dn = 0.0, dp = 0.0, uau = 0.0;
-                for (int k = 0; k < a.n_cond; ++k)
-                    if (active & (1u << k)) {
-                        dn += sums[0][k];
-                        dp += gprev[k];
-                    }
-                beta = j > 0 ? dn / dp : 0.0;
-                for (int k = 0; k < a.n_cond; ++k)
-                    if (active & (1u << k)) uau += den(k, beta);
-                alpha = dn / uau;
-                bad |= !finite_d(beta) || !finite_d(alpha);
-                for (int k = 0; k < a.n_cond; ++k) alk[k] = alpha;
-            }
+            bad |= __ballot((act || !a.per_cond) && (!finite_d(b_k) || !finite_d(al_k))) != 0;
+            beta = read_lane(b_k, c);
+            alpha = read_lane(al_k, c);
+            al_k = act || !a.per_cond ? al_k : 0.0;
+        } else {
+            al_k = 0.0;
         }
         const bool stop = bad || converged || j >= a.max_iter;
-        if (writer && t == 0) {
+        if (writer && wave == 0) {
             PcgScalars* s = a.sc;
-            s->iterations = j;
-            s->rel = rel;
-            for (int k = 0; k < a.n_cond; ++k) {
-                const double sk = sums[5][k] > 0.0 ? sums[5][k] : 1.0;
-                s->rel_cond[k] = sqrt(sums[1][k] / sk);
-                s->gam[par ^ 1][k] = sums[0][k];
+            if (on) {
+                s->rel_cond[mine] = rel_k;
+                s->gam[par ^ 1][mine] = rz_k;
+                s->alf[par ^ 1][mine] = al_k;
             }
-            s->iter_f[par ^ 1] = j + 1;
-            s->active_b = (int)active;
-            s->act_f[par ^ 1] = (int)active;
-            for (int k = 0; k < a.n_cond; ++k) s->alf[par ^ 1][k] = alk[k];
-            s->status = bad ? -4 : (converged ? 0 : (j >= a.max_iter ? -3 : 0));
-            if (stop) {
-                s->done = 1;
-                s->done_f[par ^ 1] = 1;
-            }
-            if (a.hist && !stop && j < a.hist_cap) {
-                a.hist[2 * j] = alpha;
-                a.hist[2 * j + 1] = beta;
+            if (lane == 0) {
+                s->iterations = j;
+                s->rel = rel;
+                s->iter_f[par ^ 1] = j + 1;
+                s->active_b = (int)active;
+                s->act_f[par ^ 1] = (int)active;
+                s->status = bad ? -4 : (converged ? 0 : (j >= a.max_iter ? -3 : 0));
+                if (stop) {
+                    s->done = 1;
+                    s->done_f[par ^ 1] = 1;
+                }
+                if (a.hist && !stop && j < a.hist_cap) {
+                    a.hist[2 * j] = alpha;
+                    a.hist[2 * j + 1] = beta;
+                }
             }
         }
-        a_prev = alf_prev;
+        a_prev = odd ? alf_prev : 0.0;
         if (stop || !(active & (1u << c))) {
             if (!stop && t == 0)
                 for (int q = 0; q < kStripParts; ++q) wpart[q * fs + slot] = a.fpart[par][q * fs + slot];
@@ -767,11 +859,20 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
             march(std::true_type{});
         }
     }
-    double v6[6] = {acc_rz, acc_rr, acc_zaz, acc_zau, acc_uau, acc_ss};
-    wg_sum<kStripThreads, 6>(v6);
-    if (t == 0) {
+    // sums of the workgroup: the lanes of each wavefront, then the wavefronts in order
+    __shared__ double ends[8][kStripWaves];
+    double v8[8] = {acc_rz, acc_rr, acc_zaz, acc_zau, acc_uau, acc_ss, 0.0, 0.0};
+    wave_sums<2>(v8);
+    if ((lane & 15) == 0) {
+        ends[lane >> 3][wave] = v8[0];           // value 2 (lane >> 4)
+        ends[(lane >> 3) + 1][wave] = v8[1];
+    }
+    __syncthreads();
+    if (t < (INIT ? kStripParts + 1 : kStripParts)) {
+        double v = ends[t][0];
 #pragma unroll
-        for (int q = 0; q < kStripParts; ++q) wpart[q * fs + slot] = v6[q];
-        if (INIT) a.part_ss[slot] = v6[5];
+        for (int i = 1; i < kStripWaves; ++i) v += ends[t][i];
+        double* to = t < kStripParts ? wpart + t * fs : a.part_ss;
+        to[slot] = v;
     }
 }
