@@ -32,31 +32,28 @@ struct TablesDev {
     const double *tex_f;           // at axial faces z = f dz, f=0..nz     [(nz+1) nt]
 };
 
-// Film thickness of Eq 2.3 in cancellation-free form at (cos, sin) of the angle, axial
-// position z, plus the texture depth.  e: (e1, e2) at z = 0, (e3, e4) at z = L.
+// Eccentricity (ex, ey) at the axial position t = z / L; e: (e1, e2) at z = 0, (e3, e4) at z = L.
+__device__ __forceinline__ void film_axis(const double* e, double t, double& ex, double& ey)
+{
+    ex = fma(t, e[2] - e[0], e[0]);
+    ey = fma(t, e[3] - e[1], e[1]);
+}
+
+// Film thickness of Eq 2.3 in cancellation-free form at (cos, sin) of the angle and the
+// eccentricity (ex, ey) of the axial position, plus the texture depth: q / (sqrt(R^2 + q) + R) with
+// q = c (2R + c) - 2 R_c (ex cos + ey sin) + ex^2 + ey^2.  The products are fused explicitly, so that a
+// face has the same film to the bit wherever it is evaluated.
+__device__ __forceinline__ double film_at(const GeomDev& g, double ex, double ey, double cs, double sn, double tex)
+{
+    const double q = fma(ey, ey, fma(ex, ex, fma(-(2.0 * g.Rc), fma(ex, cs, ey * sn), g.c2R)));
+    return q / (sqrt(fma(g.R, g.R, q)) + g.R) + tex;
+}
 __device__ __forceinline__ double film_h(const GeomDev& g, const double* e, double cs, double sn,
                                          double z, double tex)
 {
-    const double t = z / g.L;
-    const double ex = e[0] + (e[2] - e[0]) * t;
-    const double ey = e[1] + (e[3] - e[1]) * t;
-    const double q = g.c2R - 2.0 * g.Rc * (ex * cs + ey * sn) + ex * ex + ey * ey;
-    const double d = sqrt(g.R * g.R + q);
-    return q / (d + g.R) + tex;
-}
-
-// Time derivative of the film through the eccentricity rates (texture is fixed).
-__device__ __forceinline__ double film_rate(const GeomDev& g, const double* e, const double* ed,
-                                            double cs, double sn, double z)
-{
-    const double t = z / g.L;
-    const double ex = e[0] + (e[2] - e[0]) * t;
-    const double ey = e[1] + (e[3] - e[1]) * t;
-    const double exd = ed[0] + (ed[2] - ed[0]) * t;
-    const double eyd = ed[1] + (ed[3] - ed[1]) * t;
-    const double ax = g.Rc * cs - ex;
-    const double ay = g.Rc * sn - ey;
-    return -(ax * exd + ay * eyd) / sqrt(ax * ax + ay * ay);
+    double ex, ey;
+    film_axis(e, z / g.L, ex, ey);
+    return film_at(g, ex, ey, cs, sn, tex);
 }
 
 // Sum of NV values over a 256-thread block, fixed reduction order (wave64 shuffles, then
@@ -109,4 +106,37 @@ template <typename T>
 __device__ __forceinline__ GAP_AS1 T* as_global(T* p)
 {
     return (GAP_AS1 T*)p;
+}
+
+// One 32-bit DPP move.  ctrl 0x138: wave_shr:1 (lane i reads lane i - 1), 0x130: wave_shl:1
+// (lane i reads lane i + 1); the lane without a source keeps `fill`.
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift(double x, double fill)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned long long f = (unsigned long long)__double_as_longlong(fill);
+    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(f & 0xffffffffull), (int)(unsigned)(b & 0xffffffffull),
+                                               CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(f >> 32), (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf,
+                                               false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// The same move with BOUND_CTRL set: the lane without a source reads 0, so no fill value has
+// to be placed in the destination first.
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift0(double x)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+__device__ __forceinline__ double read_lane(double x, int l)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffull), l);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }

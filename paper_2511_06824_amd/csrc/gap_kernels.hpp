@@ -15,6 +15,13 @@ struct ChunkMap {
     int total;      // per_cond * n_cond
 };
 
+// The blocks of a force integration: per condition, row chunks times column groups (block k of a
+// condition takes the column groups k % cols, + cols, ... of row chunk k / cols).
+struct ForceMap {
+    ChunkMap cm;
+    int cols;
+};
+
 __device__ __forceinline__ void chunk_rows(const ChunkMap& cm, int nz, int b, int& c, int& j0, int& j1)
 {
     c = b / cm.per_cond;
@@ -69,51 +76,84 @@ __global__ __launch_bounds__(GAP_BLOCK) void k_texture(GeomDev g, int count, con
 }
 
 // ---------------------------------------------------------------------------------------
-// Assembly (step I): one thread per (cell, condition).  Writes the source of every
-// condition and, for conditions that own an operator, its face conductances.
-// The faces each row owns, as pairs for the strip iteration: pair (r + 1, i) holds the east
+// Assembly (step I): the face conductances of every operator and the source of every condition.
+// kxz repeats the conductances as the pairs the strip iteration reads: pair (r + 1, i) holds the east
 // face of cell (r, i) and the axial face above it, (kx(r, i), kz(r + 1, i)), for rows
-// r = -1 .. n_axial - 1 (row -1: (0, the inlet face kz(0, i))), per operator.  A row step then
-// reads its conductances with one 16-byte load per lane.
-__global__ __launch_bounds__(GAP_BLOCK) void k_pair_ops(int nt, int nz, const double* __restrict__ kx,
-                                                        const double* __restrict__ kz, double* __restrict__ kxz)
+// r = -1 .. n_axial - 1 (row -1: (0, the inlet face kz(0, i))), so that a row step reads its conductances
+// with one 16-byte load per lane.
+//
+// A wavefront marches `rows` rows of 64 columns of one operator and forms the sources of all conditions
+// that use it (their gaps are the operator's; only the squeeze term differs).  The north face of a row is
+// the south face of the next, the west face of a column the east face of its neighbour lane, and what
+// depends on z alone is formed once, row j0 + l on lane l, with the west faces of the first column: two
+// films (a square root and two divisions each) per cell and operator, where one thread per cell and
+// condition needs four.  With one thread per cell and condition and the pairs in a pass of their own,
+// 2048 x 1024 with 9 conditions took 252 + 62 us, bound by those square roots and divisions; this form
+// takes 113 us for the 540 MB it writes and reads (4.8 TB/s).  1024 x 512: 64 + 14 -> 31 us.
+constexpr int kAssembleRows = 8;        // at most: 2048 x 1024 took 139 us in chunks of 32 rows, 113 in 10, 110 in 5
+__global__ __launch_bounds__(GAP_BLOCK) void k_assemble(GeomDev g, CondDev cd, TablesDev tb, int rows,
+                                                        double* __restrict__ kx, double* __restrict__ kz,
+                                                        double* __restrict__ kxz, double* __restrict__ S)
 {
-    const int op = blockIdx.y;
-    const size_t n = (size_t)nt * nz, nf = n + nt;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;     // pair (r + 1, i)
-    if (idx >= nf) return;
-    const double e = idx >= (size_t)nt ? kx[op * n + idx - nt] : 0.0;
-    kxz[op * 2 * nf + 2 * idx] = e;
-    kxz[op * 2 * nf + 2 * idx + 1] = kz[op * nf + idx];
-}
+    const int nt = g.nt, nz = g.nz, o = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int unit = blockIdx.x * (GAP_BLOCK / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int strips = (nt + 63) / 64;
+    const int j0 = unit / strips * rows, j1 = min(j0 + rows, nz), i0 = unit % strips * 64;
+    if (j0 >= nz) return;
+    const size_t n = (size_t)nt * nz;
+    const bool on = i0 + lane < nt;
+    const int i = min(i0 + lane, nt - 1);                   // lanes past the ring repeat its last column
+    const double* e = cd.e[o];
+    // row j0 + lane: its axial position and eccentricity, those of its south face, its west face
+    const int jl = j0 + min(lane, j1 - j0);                 // one more face than rows
+    const int jr = min(jl, j1 - 1), iw = i0 ? i0 - 1 : nt - 1;
+    const double t_row = (jr + 0.5) * g.dz / g.L;
+    double ex_row, ey_row, ex_face, ey_face;
+    film_axis(e, t_row, ex_row, ey_row);
+    film_axis(e, jl * g.dz / g.L, ex_face, ey_face);
+    const double h_row = film_at(g, ex_row, ey_row, tb.cos_e[iw], tb.sin_e[iw], tb.tex_e[jr * nt + iw]);
 
-__global__ __launch_bounds__(GAP_BLOCK) void k_assemble(GeomDev g, CondDev cd, TablesDev tb, double* __restrict__ kx,
-                           double* __restrict__ kz, double* __restrict__ S)
-{
-    const int c = blockIdx.y;
-    const int n = g.nt * g.nz;
-    const int gidx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gidx >= n) return;
-    const int j = gidx / g.nt, i = gidx - j * g.nt;
-    const int iw = i ? i - 1 : g.nt - 1;
-    const double* e = cd.e[c];
-    const double zj = (j + 0.5) * g.dz;
-    const double h_e = film_h(g, e, tb.cos_e[i], tb.sin_e[i], zj, tb.tex_e[gidx]);
-    const double h_w = film_h(g, e, tb.cos_e[iw], tb.sin_e[iw], zj, tb.tex_e[j * g.nt + iw]);
-    const double h_s = film_h(g, e, tb.cos_c[i], tb.sin_c[i], j * g.dz, tb.tex_f[j * g.nt + i]);
-    const double h_n = film_h(g, e, tb.cos_c[i], tb.sin_c[i], (j + 1) * g.dz, tb.tex_f[(j + 1) * g.nt + i]);
-    const double hdot = film_rate(g, e, cd.ed[c], tb.cos_c[i], tb.sin_c[i], zj);
-    const double kfz = g.dx / g.dz / (12.0 * g.mu);
-    double s = -(0.5 * g.U) * (h_e - h_w) * g.dz - (0.5 * g.V) * (h_n - h_s) * g.dx - hdot * g.dx * g.dz;
-    if (j == 0) s += 2.0 * (h_s * h_s * h_s) * kfz * g.p_in;
-    if (j == g.nz - 1) s += 2.0 * (h_n * h_n * h_n) * kfz * g.p_out;
-    S[(size_t)c * n + gidx] = s;
-    if (c < cd.n_op) {
-        const double kfx = g.dz / g.dx / (12.0 * g.mu);
-        kx[(size_t)c * n + gidx] = (h_e * h_e * h_e) * kfx;
-        double* kzo = kz + (size_t)c * (n + g.nt);
-        kzo[gidx] = (j == 0 ? 2.0 : 1.0) * (h_s * h_s * h_s) * kfz;
-        if (j == g.nz - 1) kzo[n + i] = 2.0 * (h_n * h_n * h_n) * kfz;
+    const double cos_c = tb.cos_c[i], sin_c = tb.sin_c[i], cos_e = tb.cos_e[i], sin_e = tb.sin_e[i];
+    const double kfx = g.dz / g.dx / (12.0 * g.mu), kfz = g.dx / g.dz / (12.0 * g.mu);
+    double* kxo = kx + (size_t)o * n;
+    double* kzo = kz + (size_t)o * (n + nt);
+    double2* kxzo = (double2*)kxz + (size_t)o * (n + nt);
+    double h_s = film_at(g, read_lane(ex_face, 0), read_lane(ey_face, 0), cos_c, sin_c, tb.tex_f[j0 * nt + i]);
+    double k_s = (j0 == 0 ? 2.0 : 1.0) * (h_s * h_s * h_s) * kfz;
+    if (on && j0 == 0) kxzo[i] = make_double2(0.0, k_s);
+    for (int j = j0; j < j1; ++j) {
+        const int r = j - j0, gidx = j * nt + i;
+        const double ex = read_lane(ex_row, r), ey = read_lane(ey_row, r), t = read_lane(t_row, r);
+        const double h_n = film_at(g, read_lane(ex_face, r + 1), read_lane(ey_face, r + 1), cos_c, sin_c, tb.tex_f[gidx + nt]);
+        const double h_e = film_at(g, ex, ey, cos_e, sin_e, tb.tex_e[gidx]);
+        const double h_w = dpp_shift<0x138>(h_e, read_lane(h_row, r));
+        const double k_e = (h_e * h_e * h_e) * kfx;
+        const double k_n = (j == nz - 1 ? 2.0 : 1.0) * (h_n * h_n * h_n) * kfz;
+        if (on) {
+            kxo[gidx] = k_e;
+            kzo[gidx] = k_s;
+            if (j == nz - 1) kzo[gidx + nt] = k_n;
+            kxzo[gidx + nt] = make_double2(k_e, k_n);
+        }
+        // the squeeze rate at the cell centre, with the parts that depend on the gap alone formed once
+        const double ax = fma(g.Rc, cos_c, -ex), ay = fma(g.Rc, sin_c, -ey);
+        const double dist = sqrt(fma(ax, ax, ay * ay));
+        const double slide = fma(g.dz, -0.5 * g.U * (h_e - h_w), g.dx * (-0.5 * g.V * (h_n - h_s)));
+        for (int c = o; c < cd.n_cond; c = max(c + 1, cd.n_op)) {
+            if (cd.op[c] != o) continue;
+            const double* ed = cd.ed[c];
+            double exd, eyd;
+            film_axis(ed, t, exd, eyd);
+            const double rate = fma(ax, exd, ay * eyd) / dist;      // -dh/dt
+            // -U/2 (h_e - h_w) dz - V/2 (h_n - h_s) dx - dh/dt dx dz, fused explicitly (as in film_at)
+            double s = fma(g.dz, g.dx * rate, slide);
+            if (j == 0) s = fma(g.p_in, k_s, s);
+            if (j == nz - 1) s = fma(g.p_out, k_n, s);
+            if (on) S[(size_t)c * n + gidx] = s;
+        }
+        h_s = h_n;
+        k_s = k_n;
     }
 }
 
@@ -174,59 +214,92 @@ __device__ __forceinline__ double peff(double p, int cav, double pc) { return (c
 // NV = 4: (Fx, Fy, Mx, My) of pressure and shear together.  NV = 10: the pressure part
 // (Fx, Fy, Mx, My), then the shear part (Fx, Fy, Mx, My, Fz, Mz) with the axial force and the
 // torque of the wall shear.
+//
+// A workgroup marches the rows of a chunk down 256 columns (down the col_groups groups of a narrower
+// grid in turn): a cell's pressure is read for its own row and kept for the rows above and below, with the
+// loads of the next row sent out before a row's arithmetic; what depends on z alone is formed once per chunk
+// in the LDS, and one reciprocal of the gap serves both shear stresses.  2048 x 1024 with 9 conditions
+// (168 MB read): 140 us (4 values) and 143 us (10) with five loads and six divisions per cell, ring by ring;
+// 99 and 92 us so, about two thirds of it the arithmetic of some 115 instructions per cell.
+constexpr int kForceRows = 64;          // rows of z-dependent data held at once
 template <int NV>
-__global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, ChunkMap cm, TablesDev tb,
+__global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, ForceMap fm, TablesDev tb,
                                                       const double* __restrict__ p_all, int cav, double p_cav,
                                                       double* __restrict__ partial)
 {
-    int c, j0, j1;
-    chunk_rows(cm, g.nz, blockIdx.x, c, j0, j1);
     const int nt = g.nt, nz = g.nz;
-    const size_t n = (size_t)nt * nz;
-    const double* p = p_all + (size_t)c * n;
+    const int c = blockIdx.x / fm.cm.per_cond, k = blockIdx.x - c * fm.cm.per_cond;
+    const int j0 = k / fm.cols * fm.cm.rows, j1 = min(j0 + fm.cm.rows, nz);
+    const double* p = p_all + (size_t)c * nt * nz;
     const double* e = cd.e[c];
     double acc[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) acc[q] = 0.0;
-    for (int j = j0; j < j1; ++j) {
-        const double zj = (j + 0.5) * g.dz;
-        const double zr = zj - 0.5 * g.L;
-        for (int i = threadIdx.x; i < nt; i += blockDim.x) {
-            const int gi = j * nt + i;
+    // -1/2 over the pressure differences' distances: 2 dx, 2 dz, and 3/2 dz at the end rows
+    const double fx = -0.25 / g.dx, fz = -0.25 / g.dz, fz_end = -0.5 / (1.5 * g.dz);
+    const double mu_u = g.mu * g.U, mu_v = g.mu * g.V;
+    __shared__ double row_ex[kForceRows], row_ey[kForceRows], row_z[kForceRows];
+    for (int jb = j0; jb < j1; jb += kForceRows) {
+        const int je = min(jb + kForceRows, j1);
+        __syncthreads();
+        if ((int)threadIdx.x < je - jb) {
+            const double z = (jb + (int)threadIdx.x + 0.5) * g.dz;
+            film_axis(e, z / g.L, row_ex[threadIdx.x], row_ey[threadIdx.x]);
+            row_z[threadIdx.x] = z - 0.5 * g.L;
+        }
+        __syncthreads();
+        for (int i = k % fm.cols * GAP_BLOCK + threadIdx.x; i < nt; i += fm.cols * GAP_BLOCK) {
             const int iw = i ? i - 1 : nt - 1;
             const int ie = (i + 1 < nt) ? i + 1 : 0;
-            const double pc = peff(p[gi], cav, p_cav);
-            const double dpdx = (peff(p[j * nt + ie], cav, p_cav) - peff(p[j * nt + iw], cav, p_cav)) / (2.0 * g.dx);
-            double dpdz;
-            if (j == 0) dpdz = (peff(p[gi + nt], cav, p_cav) - g.p_in) / (1.5 * g.dz);
-            else if (j == nz - 1) dpdz = (g.p_out - peff(p[gi - nt], cav, p_cav)) / (1.5 * g.dz);
-            else dpdz = (peff(p[gi + nt], cav, p_cav) - peff(p[gi - nt], cav, p_cav)) / (2.0 * g.dz);
             const double cs = tb.cos_c[i], sn = tb.sin_c[i];
-            const double h = film_h(g, e, cs, sn, zj, tb.tex_c ? tb.tex_c[gi] : 0.0);
-            const double tt = -0.5 * h * dpdx + g.mu * g.U / h;
-            const double tz = -0.5 * h * dpdz + g.mu * g.V / h;
-            if (NV == 4) {
-                acc[0] += -pc * cs - tt * sn;
-                acc[1] += -pc * sn + tt * cs;
-                acc[2] += zr * (pc * sn - tt * cs) + tz * g.R * sn;
-                acc[3] += -zr * (pc * cs + tt * sn) - tz * g.R * cs;
-            } else {
-                acc[0] += -pc * cs;
-                acc[1] += -pc * sn;
-                acc[2] += zr * pc * sn;
-                acc[3] += -zr * pc * cs;
-                acc[4 % NV] += -tt * sn;
-                acc[5 % NV] += tt * cs;
-                acc[6 % NV] += -zr * tt * cs + tz * g.R * sn;
-                acc[7 % NV] += -zr * tt * sn - tz * g.R * cs;
-                acc[8 % NV] += tz;
-                acc[9 % NV] += g.R * tt;
+            // of row j: pressures to the south, here, north, west, east, and the texture
+            double ps = jb > 0 ? p[(jb - 1) * nt + i] : 0.0, pc = p[jb * nt + i];
+            double pn = jb + 1 < nz ? p[(jb + 1) * nt + i] : 0.0;
+            double pw = p[jb * nt + iw], pe = p[jb * nt + ie];
+            double tx = tb.tex_c ? tb.tex_c[jb * nt + i] : 0.0;
+            ps = peff(ps, cav, p_cav);
+            pc = peff(pc, cav, p_cav);
+            for (int j = jb; j < je; ++j) {
+                // the loads of row j + 1 (of row j again past the last one)
+                const int next = min(j + 1, nz - 1) * nt;
+                const double pn1 = p[min(j + 2, nz - 1) * nt + i], pw1 = p[next + iw], pe1 = p[next + ie];
+                const double tx1 = tb.tex_c ? tb.tex_c[next + i] : 0.0;
+                pn = peff(pn, cav, p_cav);
+                const double dpx = peff(pe, cav, p_cav) - peff(pw, cav, p_cav);
+                const double dpz = (j == nz - 1 ? g.p_out : pn) - (j == 0 ? g.p_in : ps);
+                const double h = film_at(g, row_ex[j - jb], row_ey[j - jb], cs, sn, tx);
+                const double zr = row_z[j - jb], inv = 1.0 / h;
+                const double tt = h * (dpx * fx) + mu_u * inv;
+                const double tz = h * (dpz * (j == 0 || j == nz - 1 ? fz_end : fz)) + mu_v * inv;
+                if (NV == 4) {
+                    acc[0] += -pc * cs - tt * sn;
+                    acc[1] += -pc * sn + tt * cs;
+                    acc[2] += zr * (pc * sn - tt * cs) + tz * g.R * sn;
+                    acc[3] += -zr * (pc * cs + tt * sn) - tz * g.R * cs;
+                } else {
+                    acc[0] += -pc * cs;
+                    acc[1] += -pc * sn;
+                    acc[2] += zr * pc * sn;
+                    acc[3] += -zr * pc * cs;
+                    acc[4 % NV] += -tt * sn;
+                    acc[5 % NV] += tt * cs;
+                    acc[6 % NV] += -zr * tt * cs + tz * g.R * sn;
+                    acc[7 % NV] += -zr * tt * sn - tz * g.R * cs;
+                    acc[8 % NV] += tz;
+                    acc[9 % NV] += g.R * tt;
+                }
+                ps = pc;
+                pc = pn;
+                pn = pn1;
+                pw = pw1;
+                pe = pe1;
+                tx = tx1;
             }
         }
     }
     block_sum<NV>(acc);
     if (threadIdx.x == 0)
-        for (int q = 0; q < NV; ++q) partial[q * cm.total + blockIdx.x] = acc[q];
+        for (int q = 0; q < NV; ++q) partial[q * fm.cm.total + blockIdx.x] = acc[q];
 }
 
 // cos and sin of the cell-centre angles theta_i = (i + 1/2) dtheta, i < nt, formed on the
@@ -249,14 +322,13 @@ __device__ __forceinline__ double cond_sum(const double* part, const ChunkMap& c
     return v[0];   // valid in thread 0
 }
 
-__global__ __launch_bounds__(GAP_BLOCK) void k_forces_finalize(ChunkMap cm, int n_cond, int nv, double dA,
+// One workgroup per condition and value (a single one took 14 us for 9 conditions of 4 values).
+__global__ __launch_bounds__(GAP_BLOCK) void k_forces_finalize(ChunkMap cm, int nv, double dA,
                                                                const double* __restrict__ part, double* __restrict__ F)
 {
-    for (int c = 0; c < n_cond; ++c)
-        for (int q = 0; q < nv; ++q) {
-            const double s = cond_sum(part + q * cm.total, cm, c);
-            if (threadIdx.x == 0) F[c * nv + q] = s * dA;
-        }
+    const int c = blockIdx.x / nv, q = blockIdx.x - c * nv;
+    const double s = cond_sum(part + q * cm.total, cm, c);
+    if (threadIdx.x == 0) F[c * nv + q] = s * dA;
 }
 
 // ||S - A p||^2 and ||S||^2 per chunk of rows, the true residual of a returned solution.

@@ -75,39 +75,6 @@ __host__ __device__ constexpr int strip_halo(int M) { return 4 * M + 2; }
 // Columns a strip of Q columns per lane owns at most.
 __host__ __device__ constexpr int strip_owned_max(int Q, int M) { return 64 * Q - 2 * strip_halo(M); }
 
-// One 32-bit DPP move.  ctrl 0x138: wave_shr:1 (lane i reads lane i - 1), 0x130: wave_shl:1
-// (lane i reads lane i + 1); the lane without a source keeps `fill`.
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift(double x, double fill)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const unsigned long long f = (unsigned long long)__double_as_longlong(fill);
-    const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)(f & 0xffffffffull), (int)(unsigned)(b & 0xffffffffull),
-                                               CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(f >> 32), (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf,
-                                               false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// The same move with BOUND_CTRL set: the lane without a source reads 0, so no fill value has
-// to be placed in the destination first.
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift0(double x)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-__device__ __forceinline__ double read_lane(double x, int l)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffull), l);
-    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // First ring column that strip i of n_strips owns, floor(i n_theta / n_strips): in 32 bits wherever
 // the products fit (a 64-bit division takes some hundred instructions).
 __device__ __forceinline__ int strip_column(int i, int nt, int n_strips)

@@ -58,6 +58,8 @@ bool is_finite(double x) { return std::isfinite(x); }
     } while (0)
 
 constexpr int kTargetChunks = 2048;
+constexpr int kForceBlocks = 6 * 256;     // blocks a force integration aims at
+constexpr int kAssembleWaves = 8192;    // wavefronts an assembly launch aims at
 constexpr int kMaxThetaCells = 16384;
 constexpr int kMaxRingCells = 2048;     // kernels whose workgroups hold whole rings
 constexpr int kMaxAxialCells = 65536;
@@ -71,6 +73,23 @@ ChunkMap make_chunks(int nz, int n_cond)
     cm.per_cond = (nz + cm.rows - 1) / cm.rows;
     cm.total = cm.per_cond * n_cond;
     return cm;
+}
+
+// Blocks of a force integration: six per CU (what its registers allow) in one round, and never more than
+// make_chunks gives, for which the partial sums have room.  A block takes two column groups half a ring
+// apart: the mean pressure, whose force cancels around the ring, cancels in it and not in the final sum
+// (one group per block left 30 times the rounding error).
+ForceMap make_force_map(int nt, int nz, int n_cond)
+{
+    ForceMap fm;
+    const int room = make_chunks(nz, n_cond).per_cond;
+    const int per = std::max(1, std::min(room, kForceBlocks / n_cond));
+    fm.cols = std::clamp((nt + GAP_BLOCK - 1) / GAP_BLOCK / 2, 1, per);
+    const int chunks = per / fm.cols;
+    fm.cm.rows = (nz + chunks - 1) / chunks;
+    fm.cm.per_cond = (nz + fm.cm.rows - 1) / fm.cm.rows * fm.cols;
+    fm.cm.total = fm.cm.per_cond * n_cond;
+    return fm;
 }
 
 // Kernel shape of the PCG iteration kernels: NT threads per workgroup, Q ring columns per
@@ -514,7 +533,7 @@ struct gap_grid_s {
     double *dim_dev = nullptr, *dim_host = nullptr;          // dimple parameters for set_gap_dimples (host: pinned)
     int dim_cap = 0;                                         // dimples they hold
     double *kx = nullptr, *kz = nullptr, *minv = nullptr;
-    double *kxz = nullptr;                                   // kx and kz as the pairs of k_pair_ops
+    double *kxz = nullptr;                                   // kx and kz as the pairs k_assemble describes
     double *S = nullptr, *r0 = nullptr, *r1 = nullptr, *u0 = nullptr, *u1 = nullptr, *z = nullptr;
     double *z1 = nullptr;                                    // second z of the one-launch iteration
     double *partial = nullptr;                               // force-integration partials
@@ -1481,12 +1500,14 @@ gap_status assemble_joint_system(gap_grid_t g, const double e[4], const double e
     }
     hipStream_t st = (hipStream_t)stream;
     const TablesDev t = g->tables();
-    hipLaunchKernelGGL(k_assemble, dim3((unsigned)((g->n + GAP_BLOCK - 1) / GAP_BLOCK), n_cond), dim3(GAP_BLOCK), 0, st,
-                       g->gd, cd, t, g->kx, g->kz, g->S);
+    // rows a wavefront marches: as many as leave eight wavefronts per SIMD (1024 x 512 with 9 conditions:
+    // 33 us with four per SIMD, 31 with eight, 34 with sixteen)
+    const long long strips = (g->nt + 63) / 64;
+    const int rows = (int)std::clamp<long long>(strips * g->nz * cd.n_op / kAssembleWaves, 1, kAssembleRows);
+    const long long units = strips * ((g->nz + rows - 1) / rows);
+    hipLaunchKernelGGL(k_assemble, dim3((unsigned)((units + GAP_BLOCK / 64 - 1) / (GAP_BLOCK / 64)), cd.n_op),
+                       dim3(GAP_BLOCK), 0, st, g->gd, cd, t, rows, g->kx, g->kz, g->kxz, g->S);
     HIPLAUNCHCHK("k_assemble");
-    hipLaunchKernelGGL(k_pair_ops, dim3((unsigned)((g->n + g->nt + GAP_BLOCK - 1) / GAP_BLOCK), cd.n_op),
-                       dim3(GAP_BLOCK), 0, st, g->nt, g->nz, (const double*)g->kx, (const double*)g->kz, g->kxz);
-    HIPLAUNCHCHK("k_pair_ops");
     g->cd = cd;
     g->n_cond = n_cond;
     g->n_op = cd.n_op;
@@ -1536,7 +1557,7 @@ gap_status solve_joint_pcg(gap_grid_t g, const gap_solver_opts* o, double* p, ga
             gap_status s1 = dmalloc(&g->step_buf, 36 + 32);
             if (s1 != GAP_OK) return s1;
         }
-        hipLaunchKernelGGL(k_forces_finalize, dim3(1), dim3(GAP_BLOCK), 0, st, cm, g->n_cond, 2, 1.0,
+        hipLaunchKernelGGL(k_forces_finalize, dim3(g->n_cond * 2), dim3(GAP_BLOCK), 0, st, cm, 2, 1.0,
                            (const double*)g->partial, g->step_buf);
         HIPLAUNCHCHK("residual sums");
         double sums[2 * GAP_MAX_COND];
@@ -1816,10 +1837,10 @@ gap_status integrate_force_moment(gap_grid_t g, const double* p, int32_t cavitat
     gap_status cs = check_integrate(g, p, F, cavitation, p_cav, "integrate_force_moment");
     if (cs != GAP_OK) return cs;
     hipStream_t st = (hipStream_t)stream;
-    const ChunkMap cm = g->cm;
-    hipLaunchKernelGGL((k_forces<4>), dim3(cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, cm, g->tables(), p,
+    const ForceMap fm = make_force_map(g->nt, g->nz, g->n_cond);
+    hipLaunchKernelGGL((k_forces<4>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, fm, g->tables(), p,
                        cavitation, p_cav, g->partial);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(1), dim3(GAP_BLOCK), 0, st, cm, g->n_cond, 4, g->gd.dx * g->gd.dz,
+    hipLaunchKernelGGL(k_forces_finalize, dim3(g->n_cond * 4), dim3(GAP_BLOCK), 0, st, fm.cm, 4, g->gd.dx * g->gd.dz,
                        (const double*)g->partial, F);
     HIPLAUNCHCHK("force integration");
     return GAP_OK;
@@ -1831,10 +1852,10 @@ gap_status integrate_force_moment_split(gap_grid_t g, const double* p, int32_t c
     gap_status cs = check_integrate(g, p, F, cavitation, p_cav, "integrate_force_moment_split");
     if (cs != GAP_OK) return cs;
     hipStream_t st = (hipStream_t)stream;
-    const ChunkMap cm = g->cm;
-    hipLaunchKernelGGL((k_forces<10>), dim3(cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, cm, g->tables(), p,
+    const ForceMap fm = make_force_map(g->nt, g->nz, g->n_cond);
+    hipLaunchKernelGGL((k_forces<10>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, fm, g->tables(), p,
                        cavitation, p_cav, g->partial);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(1), dim3(GAP_BLOCK), 0, st, cm, g->n_cond, 10, g->gd.dx * g->gd.dz,
+    hipLaunchKernelGGL(k_forces_finalize, dim3(g->n_cond * 10), dim3(GAP_BLOCK), 0, st, fm.cm, 10, g->gd.dx * g->gd.dz,
                        (const double*)g->partial, F);
     HIPLAUNCHCHK("split force integration");
     return GAP_OK;
@@ -1915,12 +1936,13 @@ gap_status integrate_force_moment_noalloc(const gap_geom* geom, int32_t n_cond, 
     tb.sin_c = ws + nt;
     tb.tex_c = tex_c;
     double* part = ws + 2 * nt;
+    const ForceMap fm = make_force_map(nt, geom->n_axial, n_cond);
     hipStream_t hs = (hipStream_t)stream;
     hipLaunchKernelGGL(k_trig_centres, dim3((nt + GAP_BLOCK - 1) / GAP_BLOCK), dim3(GAP_BLOCK), 0, hs, nt, gd.dth, ws,
                        ws + nt);
-    hipLaunchKernelGGL((k_forces<4>), dim3(cm.total), dim3(GAP_BLOCK), 0, hs, gd, cd, cm, tb, p, cavitation, p_cav,
+    hipLaunchKernelGGL((k_forces<4>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, hs, gd, cd, fm, tb, p, cavitation, p_cav,
                        part);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(1), dim3(GAP_BLOCK), 0, hs, cm, n_cond, 4, gd.dx * gd.dz,
+    hipLaunchKernelGGL(k_forces_finalize, dim3(n_cond * 4), dim3(GAP_BLOCK), 0, hs, fm.cm, 4, gd.dx * gd.dz,
                        (const double*)part, F);
     HIPLAUNCHCHK("handle-free force integration");
     return GAP_OK;
