@@ -95,6 +95,7 @@ struct PcgDev {
     // strip iteration (gap_pcgw.hpp): strips per ring and strip groups (workgroups) per row
     // chunk; chunks_b counts row chunks x groups, rows_b the rows of a row chunk
     int n_strips, strip_groups;
+    int p_stays;                // strip iteration: p is read without the streaming hint (kCachedBytes)
 };
 
 // A launch covers one or more joint systems ("requests"), each described by a PcgDev in

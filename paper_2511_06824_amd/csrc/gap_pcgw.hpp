@@ -362,6 +362,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
         for (int k = 0; k < M; ++k) T[k][q] = TQ[k][q] = 0.0;
         ZQ[q] = kwc[q] = yc[q] = 0.0;
     }
+    const bool p_stays = a.p_stays != 0;
     // u_{j-1} is read from the second iteration on (beta = 0 before), p_0 on a warm start
     const bool need_up = INIT ? a.warm != 0 : has_prev;
     // loads of row step s into ring slot SL: r, u_prev (p_0), kx of row s; face s + 1; p of
@@ -392,8 +393,12 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
             if (!kPairs && s - M >= 0 && s - M < nz && need_up)
                 UP[sl][q] = __builtin_nontemporal_load(&uin[(unsigned)(s - M) * nt + gc]);
             if (!kPairs && s + 1 <= nz) F[sl][q] = kz[(unsigned)(s + 1) * nt + gc];
-            if (odd && ownc[q] && s - M - 1 >= j0 && s - M - 1 < j1)
-                PP[sl][q] = __builtin_nontemporal_load(&pp[(unsigned)(s - M - 1) * nt + gc]);
+            if (odd && ownc[q] && s - M - 1 >= j0 && s - M - 1 < j1) {
+                const GAP_AS1 double* at = &pp[(unsigned)(s - M - 1) * nt + gc];
+                // (a plain load would be merged with the other one, without the hint)
+                if (kPairs && p_stays) PP[sl][q] = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                else PP[sl][q] = __builtin_nontemporal_load(at);
+            }
             if (pk == 1) {
                 if (s - 1 >= 0 && s - 1 < nz) MV1[sl][q] = mv[(unsigned)(s - 1) * nt + gc];
                 if (s - 3 >= 0 && s - 3 < nz) MV3[sl][q] = mv[(unsigned)(s - 3) * nt + gc];

@@ -233,6 +233,14 @@ inline double strip_request_bytes(const PcgDev& a)
     return (double)a.nt * a.nz * (40.0 * a.n_cond + 16.0 * n_op);
 }
 
+// A request whose iterations touch less than this keeps its whole state in the 256 MB last-level cache from
+// one launch to the next, p included: the strip kernel then reads p without the non-temporal hint, which
+// would take its lines out of that cache (in a batch the rule looks at each request alone, as its chunks do).
+// us per iteration with and without the hint, 9 conditions:
+// 640 x 480 (129 MiB) 37.4 and 34.4, 1024 x 512 (220) 51.0 and 47.4, 1060 x 550 (245) 61.7 and 55.8,
+// 1080 x 560 (254) 63.4 and 64.3, 800 x 760 (255) 61.3 and 62.9, 1400 x 700 (411) 105.9 and 105.6.
+constexpr double kCachedBytes = 248.0 * 1024 * 1024;
+
 // Whether a request of order M runs the synchronized march.
 inline bool strip_sync(int M, const PcgDev& a) { return M == 1 && strip_request_bytes(a) >= kStripSyncBytes; }
 
@@ -269,6 +277,7 @@ void strip_chunks(int nz, int nt, int n_cond, int Q, int M, int slots, PcgDev& a
     a.strip_groups = groups;
     a.rows_b = a.rows_a = rows;
     a.chunks_b = a.chunks_a = chunks * groups;
+    a.p_stays = strip_request_bytes(a) < kCachedBytes;
 }
 
 // The strip kernels of Q columns per lane: the initial residual (preconditioner read from
