@@ -36,8 +36,9 @@
 // one pass from the state that the previous launch left in memory and waits for nothing: that
 // form serves kernel timing and the solve after a wait given up, and gives the same bits.
 //
-// Measured per iteration, launches of k_pcg_w before and this kernel now: 64 x 32 x 1 18.9 -> 4.3 us,
-// 128 x 64 x 9 21.2 -> 4.2, 256 x 128 x 9 21.6 -> 5.1, 512 x 256 x 9 29.6 -> 8.5, 400 x 360 x 9 30.9 -> 9.3.
+// Measured per iteration, launches of k_pcg_w and this kernel: 64 x 32 x 1 15.6 and 4.0 us, 128 x 64 x 9
+// 16.2 and 4.1, 256 x 128 x 9 16.9 and 5.0, 512 x 256 x 9 21.8 and 8.6, 400 x 360 x 9 22.9 and 9.3 (18.9, 21.2,
+// 21.6, 29.6 and 30.9 with the launches as they were when this kernel came in).
 // Of the 4.2 us at 128 x 64 the march over 4 rows takes 0.7 (62 instructions a row, issued one each
 // 4 cycles: FP64 rate), the exchange 1.7 (one store to one load across the fabric takes 0.9 at least),
 // the two sums over lanes 0.6, the scalars 0.8 (two dependent divisions); at 512 x 256 the march over
