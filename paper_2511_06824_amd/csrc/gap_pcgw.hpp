@@ -444,7 +444,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_pcg_w(const PcgDev* __rest
         double rel_k = 0.0;
         if (a.async || writer) rel_k = sqrt(rr_k / (ss_k > 0.0 ? ss_k : 1.0));
         if (a.async) active = (unsigned)__ballot(on && ((was_active >> mine) & 1) && rel_k > eps_mine);
-        const bool act = (active >> lane) & (lane < 32);
+        const bool act = on && ((active >> mine) & 1);
         // sums over the conditions in their order, one per lane: r.r, S.S, and of the active ones
         // r.z and the previous r.z (a condition left out adds +0 to a sum that is never -0)
         const double* col = sums + ((0x6051 >> (4 * (lane & 3))) & 7);
