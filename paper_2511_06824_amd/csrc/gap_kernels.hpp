@@ -15,13 +15,6 @@ struct ChunkMap {
     int total;      // per_cond * n_cond
 };
 
-// The blocks of a force integration: per condition, row chunks times column groups (block k of a
-// condition takes the column groups k % cols, + cols, ... of row chunk k / cols).
-struct ForceMap {
-    ChunkMap cm;
-    int cols;
-};
-
 __device__ __forceinline__ void chunk_rows(const ChunkMap& cm, int nz, int b, int& c, int& j0, int& j1)
 {
     c = b / cm.per_cond;
@@ -215,21 +208,32 @@ __device__ __forceinline__ double peff(double p, int cav, double pc) { return (c
 // (Fx, Fy, Mx, My), then the shear part (Fx, Fy, Mx, My, Fz, Mz) with the axial force and the
 // torque of the wall shear.
 //
-// A workgroup marches the rows of a chunk down 256 columns (down the col_groups groups of a narrower
-// grid in turn): a cell's pressure is read for its own row and kept for the rows above and below, with the
-// loads of the next row sent out before a row's arithmetic; what depends on z alone is formed once per chunk
-// in the LDS, and one reciprocal of the gap serves both shear stresses.  2048 x 1024 with 9 conditions
-// (168 MB read): 140 us (4 values) and 143 us (10) with five loads and six divisions per cell, ring by ring;
-// 99 and 92 us so, about two thirds of it the arithmetic of some 115 instructions per cell.
+// A workgroup takes the whole rings of a chunk of rows, ring by ring, thread t the columns t, t + 256, ...: what
+// cancels around a ring, the mean pressure and every harmonic but the first, cancels while the terms are
+// added.  (Columns marched down the rows, two groups of 256 to a workgroup, take 94 us where this takes 105, but
+// cancel only in the final sum: up to 30 times the error of the ring order where a third harmonic is strong.)
+//
+// LDS: the pressures of a row and of the row below it are kept there (rings up to kForceRing columns), so that each is
+// read from memory once per chunk; three rows of every resident workgroup do not fit an L2.  The loads of a thread's
+// next two cells are in flight during the arithmetic of the present two (with one, a pass over assembly, forces, split
+// and field at 2048 x 1024 took 408 us, with two 393, with four, whose registers leave fewer wavefronts, 407), what
+// depends on z alone is formed once per chunk, and one reciprocal of the gap serves both shear stresses.  A call at
+// 2048 x 1024 with 9 conditions (168 MB read), 4 and 10 values: 156 and 184 us with loads where they are used, six
+// divisions per cell and a single workgroup for the final sums, 123 and 117 us without the rows in the LDS, 105 and 101
+// us so, about half of it the arithmetic of some 115 instructions per cell.  3072 x 600: 138 and 168, 111 and 108, 97
+// and 95 us.  Longer rings would leave one or two workgroups per CU.
 constexpr int kForceRows = 64;          // rows of z-dependent data held at once
-template <int NV>
-__global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, ForceMap fm, TablesDev tb,
+constexpr int kForceRing = 3072;        // columns of a ring kept in the LDS
+constexpr int kForceAhead = 2;          // cells whose loads a thread has in flight
+template <int NV, bool LDS>
+__global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, ChunkMap cm, TablesDev tb,
                                                       const double* __restrict__ p_all, int cav, double p_cav,
                                                       double* __restrict__ partial)
 {
-    const int nt = g.nt, nz = g.nz;
-    const int c = blockIdx.x / fm.cm.per_cond, k = blockIdx.x - c * fm.cm.per_cond;
-    const int j0 = k / fm.cols * fm.cm.rows, j1 = min(j0 + fm.cm.rows, nz);
+    extern __shared__ double ring[];    // two rows of nt pressures
+    int c, j0, j1;
+    chunk_rows(cm, g.nz, blockIdx.x, c, j0, j1);
+    const int nt = g.nt, nz = g.nz, t = threadIdx.x;
     const double* p = p_all + (size_t)c * nt * nz;
     const double* e = cd.e[c];
     double acc[NV];
@@ -239,38 +243,64 @@ __global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, For
     const double fx = -0.25 / g.dx, fz = -0.25 / g.dz, fz_end = -0.5 / (1.5 * g.dz);
     const double mu_u = g.mu * g.U, mu_v = g.mu * g.V;
     __shared__ double row_ex[kForceRows], row_ey[kForceRows], row_z[kForceRows];
+    if (LDS)
+        for (int i = t; i < nt; i += GAP_BLOCK) {
+            ring[i] = j0 > 0 ? peff(p[(j0 - 1) * nt + i], cav, p_cav) : 0.0;
+            ring[nt + i] = peff(p[j0 * nt + i], cav, p_cav);
+        }
+    // what a cell loads: its pressure to the north, texture depth and angle; kForceAhead columns at a time
+    struct Cell {
+        double pn, tx, cs, sn;
+    };
+    auto load = [&](int j, int i) {
+        Cell x;
+        x.pn = p[min(j + 1, nz - 1) * nt + i];
+        x.tx = tb.tex_c ? tb.tex_c[j * nt + i] : 0.0;
+        x.cs = tb.cos_c[i];
+        x.sn = tb.sin_c[i];
+        return x;
+    };
     for (int jb = j0; jb < j1; jb += kForceRows) {
         const int je = min(jb + kForceRows, j1);
         __syncthreads();
-        if ((int)threadIdx.x < je - jb) {
-            const double z = (jb + (int)threadIdx.x + 0.5) * g.dz;
-            film_axis(e, z / g.L, row_ex[threadIdx.x], row_ey[threadIdx.x]);
-            row_z[threadIdx.x] = z - 0.5 * g.L;
+        if (t < je - jb) {
+            const double z = (jb + t + 0.5) * g.dz;
+            film_axis(e, z / g.L, row_ex[t], row_ey[t]);
+            row_z[t] = z - 0.5 * g.L;
         }
         __syncthreads();
-        for (int i = k % fm.cols * GAP_BLOCK + threadIdx.x; i < nt; i += fm.cols * GAP_BLOCK) {
-            const int iw = i ? i - 1 : nt - 1;
-            const int ie = (i + 1 < nt) ? i + 1 : 0;
-            const double cs = tb.cos_c[i], sn = tb.sin_c[i];
-            // of row j: pressures to the south, here, north, west, east, and the texture
-            double ps = jb > 0 ? p[(jb - 1) * nt + i] : 0.0, pc = p[jb * nt + i];
-            double pn = jb + 1 < nz ? p[(jb + 1) * nt + i] : 0.0;
-            double pw = p[jb * nt + iw], pe = p[jb * nt + ie];
-            double tx = tb.tex_c ? tb.tex_c[jb * nt + i] : 0.0;
-            ps = peff(ps, cav, p_cav);
-            pc = peff(pc, cav, p_cav);
-            for (int j = jb; j < je; ++j) {
-                // the loads of row j + 1 (of row j again past the last one)
-                const int next = min(j + 1, nz - 1) * nt;
-                const double pn1 = p[min(j + 2, nz - 1) * nt + i], pw1 = p[next + iw], pe1 = p[next + ie];
-                const double tx1 = tb.tex_c ? tb.tex_c[next + i] : 0.0;
-                pn = peff(pn, cav, p_cav);
-                const double dpx = peff(pe, cav, p_cav) - peff(pw, cav, p_cav);
-                const double dpz = (j == nz - 1 ? g.p_out : pn) - (j == 0 ? g.p_in : ps);
-                const double h = film_at(g, row_ex[j - jb], row_ey[j - jb], cs, sn, tx);
-                const double zr = row_z[j - jb], inv = 1.0 / h;
+        Cell next[kForceAhead];
+        auto load_ahead = [&](int j, int i0) {
+#pragma unroll
+            for (int b = 0; b < kForceAhead; ++b) next[b] = load(j, min(i0 + b * GAP_BLOCK, nt - 1));
+        };
+        load_ahead(jb, t);
+        for (int j = jb; j < je; ++j) {
+            double* const below = ring + ((j - j0) & 1 ? nt : 0);
+            const double* const here = ring + ((j - j0) & 1 ? 0 : nt);
+            const double ex = row_ex[j - jb], ey = row_ey[j - jb], zr = row_z[j - jb];
+            const double f_z = j == 0 || j == nz - 1 ? fz_end : fz;
+            auto cell = [&](int i, const Cell& x) {
+                const int iw = i ? i - 1 : nt - 1, ie = i + 1 < nt ? i + 1 : 0;
+                const double pn = peff(x.pn, cav, p_cav);
+                double pc, pw, pe, ps;
+                if (LDS) {
+                    pc = here[i];
+                    pw = here[iw];
+                    pe = here[ie];
+                    ps = below[i];
+                    below[i] = pn;                      // the row above takes its place
+                } else {
+                    const double* row = p + j * nt;
+                    pc = peff(row[i], cav, p_cav);
+                    pw = peff(row[iw], cav, p_cav);
+                    pe = peff(row[ie], cav, p_cav);
+                    ps = j > 0 ? peff(row[i - nt], cav, p_cav) : 0.0;
+                }
+                const double dpx = pe - pw, dpz = (j == nz - 1 ? g.p_out : pn) - (j == 0 ? g.p_in : ps);
+                const double cs = x.cs, sn = x.sn, h = film_at(g, ex, ey, cs, sn, x.tx), inv = 1.0 / h;
                 const double tt = h * (dpx * fx) + mu_u * inv;
-                const double tz = h * (dpz * (j == 0 || j == nz - 1 ? fz_end : fz)) + mu_v * inv;
+                const double tz = h * (dpz * f_z) + mu_v * inv;
                 if (NV == 4) {
                     acc[0] += -pc * cs - tt * sn;
                     acc[1] += -pc * sn + tt * cs;
@@ -288,18 +318,23 @@ __global__ __launch_bounds__(GAP_BLOCK) void k_forces(GeomDev g, CondDev cd, For
                     acc[8 % NV] += tz;
                     acc[9 % NV] += g.R * tt;
                 }
-                ps = pc;
-                pc = pn;
-                pn = pn1;
-                pw = pw1;
-                pe = pe1;
-                tx = tx1;
+            };
+            for (int i0 = t; i0 < nt; i0 += kForceAhead * GAP_BLOCK) {
+                Cell now[kForceAhead];
+#pragma unroll
+                for (int b = 0; b < kForceAhead; ++b) now[b] = next[b];
+                const bool more = i0 + kForceAhead * GAP_BLOCK < nt;
+                load_ahead(more ? j : min(j + 1, je - 1), more ? i0 + kForceAhead * GAP_BLOCK : t);
+#pragma unroll
+                for (int b = 0; b < kForceAhead; ++b)
+                    if (i0 + b * GAP_BLOCK < nt) cell(i0 + b * GAP_BLOCK, now[b]);
             }
+            if (LDS) __syncthreads();                   // the row above is complete
         }
     }
     block_sum<NV>(acc);
-    if (threadIdx.x == 0)
-        for (int q = 0; q < NV; ++q) partial[q * fm.cm.total + blockIdx.x] = acc[q];
+    if (t == 0)
+        for (int q = 0; q < NV; ++q) partial[q * cm.total + blockIdx.x] = acc[q];
 }
 
 // cos and sin of the cell-centre angles theta_i = (i + 1/2) dtheta, i < nt, formed on the

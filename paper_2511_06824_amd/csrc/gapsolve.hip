@@ -58,7 +58,8 @@ bool is_finite(double x) { return std::isfinite(x); }
     } while (0)
 
 constexpr int kTargetChunks = 2048;
-constexpr int kForceBlocks = 6 * 256;     // blocks a force integration aims at
+constexpr int kForcePerCu = 4;          // workgroups of a force integration per CU at most
+constexpr int kForceLds = 160 * 1024;
 constexpr int kAssembleWaves = 8192;    // wavefronts an assembly launch aims at
 constexpr int kMaxThetaCells = 16384;
 constexpr int kMaxRingCells = 2048;     // kernels whose workgroups hold whole rings
@@ -75,21 +76,33 @@ ChunkMap make_chunks(int nz, int n_cond)
     return cm;
 }
 
-// Blocks of a force integration: six per CU (what its registers allow) in one round, and never more than
-// make_chunks gives, for which the partial sums have room.  A block takes two column groups half a ring
-// apart: the mean pressure, whose force cancels around the ring, cancels in it and not in the final sum
-// (one group per block left 30 times the rounding error).
-ForceMap make_force_map(int nt, int nz, int n_cond)
+// Row chunks of a force integration: as many workgroups as the CUs hold at once (four by their registers, fewer where
+// rings in the LDS are long), and never more than make_chunks gives, for which the partial sums have room.
+ChunkMap make_force_chunks(int nt, int nz, int n_cond)
 {
-    ForceMap fm;
-    const int room = make_chunks(nz, n_cond).per_cond;
-    const int per = std::max(1, std::min(room, kForceBlocks / n_cond));
-    fm.cols = std::clamp((nt + GAP_BLOCK - 1) / GAP_BLOCK / 2, 1, per);
-    const int chunks = per / fm.cols;
-    fm.cm.rows = (nz + chunks - 1) / chunks;
-    fm.cm.per_cond = (nz + fm.cm.rows - 1) / fm.cm.rows * fm.cols;
-    fm.cm.total = fm.cm.per_cond * n_cond;
-    return fm;
+    ChunkMap cm;
+    const int per_cu = nt <= kForceRing ? std::min(kForcePerCu, kForceLds / (16 * nt + 2048)) : kForcePerCu;
+    const int per = std::max(1, std::min(make_chunks(nz, n_cond).per_cond, 256 * per_cu / n_cond));
+    cm.rows = (nz + per - 1) / per;
+    cm.per_cond = (nz + cm.rows - 1) / cm.rows;
+    cm.total = cm.per_cond * n_cond;
+    return cm;
+}
+
+// Force integration of n_cond conditions in NV values each (k_forces), then the sums of its chunks.
+template <int NV>
+void launch_forces(const GeomDev& gd, const CondDev& cd, int n_cond, const TablesDev& tb, const double* p, int cavitation,
+                   double p_cav, double* part, double* F, hipStream_t st)
+{
+    const ChunkMap cm = make_force_chunks(gd.nt, gd.nz, n_cond);
+    if (gd.nt <= kForceRing)
+        hipLaunchKernelGGL((k_forces<NV, true>), dim3(cm.total), dim3(GAP_BLOCK), 2 * gd.nt * sizeof(double), st, gd, cd,
+                           cm, tb, p, cavitation, p_cav, part);
+    else
+        hipLaunchKernelGGL((k_forces<NV, false>), dim3(cm.total), dim3(GAP_BLOCK), 0, st, gd, cd, cm, tb, p, cavitation,
+                           p_cav, part);
+    hipLaunchKernelGGL(k_forces_finalize, dim3(n_cond * NV), dim3(GAP_BLOCK), 0, st, cm, NV, gd.dx * gd.dz,
+                       (const double*)part, F);
 }
 
 // Kernel shape of the PCG iteration kernels: NT threads per workgroup, Q ring columns per
@@ -1846,11 +1859,7 @@ gap_status integrate_force_moment(gap_grid_t g, const double* p, int32_t cavitat
     gap_status cs = check_integrate(g, p, F, cavitation, p_cav, "integrate_force_moment");
     if (cs != GAP_OK) return cs;
     hipStream_t st = (hipStream_t)stream;
-    const ForceMap fm = make_force_map(g->nt, g->nz, g->n_cond);
-    hipLaunchKernelGGL((k_forces<4>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, fm, g->tables(), p,
-                       cavitation, p_cav, g->partial);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(g->n_cond * 4), dim3(GAP_BLOCK), 0, st, fm.cm, 4, g->gd.dx * g->gd.dz,
-                       (const double*)g->partial, F);
+    launch_forces<4>(g->gd, g->cd, g->n_cond, g->tables(), p, cavitation, p_cav, g->partial, F, st);
     HIPLAUNCHCHK("force integration");
     return GAP_OK;
 }
@@ -1861,11 +1870,7 @@ gap_status integrate_force_moment_split(gap_grid_t g, const double* p, int32_t c
     gap_status cs = check_integrate(g, p, F, cavitation, p_cav, "integrate_force_moment_split");
     if (cs != GAP_OK) return cs;
     hipStream_t st = (hipStream_t)stream;
-    const ForceMap fm = make_force_map(g->nt, g->nz, g->n_cond);
-    hipLaunchKernelGGL((k_forces<10>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, st, g->gd, g->cd, fm, g->tables(), p,
-                       cavitation, p_cav, g->partial);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(g->n_cond * 10), dim3(GAP_BLOCK), 0, st, fm.cm, 10, g->gd.dx * g->gd.dz,
-                       (const double*)g->partial, F);
+    launch_forces<10>(g->gd, g->cd, g->n_cond, g->tables(), p, cavitation, p_cav, g->partial, F, st);
     HIPLAUNCHCHK("split force integration");
     return GAP_OK;
 }
@@ -1945,14 +1950,10 @@ gap_status integrate_force_moment_noalloc(const gap_geom* geom, int32_t n_cond, 
     tb.sin_c = ws + nt;
     tb.tex_c = tex_c;
     double* part = ws + 2 * nt;
-    const ForceMap fm = make_force_map(nt, geom->n_axial, n_cond);
     hipStream_t hs = (hipStream_t)stream;
     hipLaunchKernelGGL(k_trig_centres, dim3((nt + GAP_BLOCK - 1) / GAP_BLOCK), dim3(GAP_BLOCK), 0, hs, nt, gd.dth, ws,
                        ws + nt);
-    hipLaunchKernelGGL((k_forces<4>), dim3(fm.cm.total), dim3(GAP_BLOCK), 0, hs, gd, cd, fm, tb, p, cavitation, p_cav,
-                       part);
-    hipLaunchKernelGGL(k_forces_finalize, dim3(n_cond * 4), dim3(GAP_BLOCK), 0, hs, fm.cm, 4, gd.dx * gd.dz,
-                       (const double*)part, F);
+    launch_forces<4>(gd, cd, n_cond, tb, p, cavitation, p_cav, part, F, hs);
     HIPLAUNCHCHK("handle-free force integration");
     return GAP_OK;
 }
