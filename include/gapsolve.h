@@ -397,6 +397,17 @@ enum {
 gap_status gap_kernel_timing(gap_grid_t grid, int32_t enable);
 gap_status gap_kernel_stats(gap_grid_t grid, int32_t kernel, int64_t *launches, double *total_ms);
 
+/* Measurement support: which way the last solve of this handle ran (solve_joint_pcg or a solve inside
+ * jacobian_adjoint, solve_with_adjoint, general_iteration_step; not as a batch member).
+ *   GAP_PCG_PATH_NONE      no solve yet
+ *   GAP_PCG_PATH_LAUNCHES  launches of the iteration kernel the options name
+ *   GAP_PCG_PATH_RESIDENT  the resident kernel (gap_solver_opts, graph)
+ *   GAP_PCG_PATH_GAVE_UP   the resident kernel was refused or gave up waiting for workgroups that other
+ *                          work kept off the device; the solve was started again without it
+ * Errors: GAP_EINVAL (NULL argument). */
+enum { GAP_PCG_PATH_NONE = 0, GAP_PCG_PATH_LAUNCHES = 1, GAP_PCG_PATH_RESIDENT = 2, GAP_PCG_PATH_GAVE_UP = 3 };
+gap_status gap_pcg_path(gap_grid_t grid, int32_t *path);
+
 /* Measurement support: record the PCG scalars of every iteration of the following solves of
  * this handle (Table 1 steps 3 and 9): alpha_j and beta_{j-1}, the beta that formed u_j (0 at
  * j = 0), for iterations j < capacity.  With GLOBAL scalars they are the joint recurrence's;

@@ -576,6 +576,7 @@ struct gap_grid_s {
     unsigned loop_base = 0;                                  // passes numbered so far
     bool loop_clear = true;                                  // the words hold unknown passes
     double* loop_p0 = nullptr;                               // warm start: the initial guess, should a launch give up
+    int path = GAP_PCG_PATH_NONE;                            // which way the last solve ran
     double *adj_rhs = nullptr, *adj_lam = nullptr;           // adjoint right-hand sides and solutions
     double *adj_part = nullptr;                              // sensitivity partials
     double *step_buf = nullptr;                              // general iteration: F (9 x 4) and J (4 x 8)
@@ -811,6 +812,7 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
             }
         }
         if (!gave_up) return GAP_OK;
+        g->path = GAP_PCG_PATH_GAVE_UP;
         if (a.warm) HIPCHK(hipMemcpyAsync(a.p, g->loop_p0, p_bytes, hipMemcpyDeviceToDevice, st));
         ss = start();
         if (ss != GAP_OK) return ss;
@@ -862,6 +864,7 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     const bool blocks_ok = o->graph != 0 || check_every >= kLoopMinBlock;
     const int loop_rows = strip && o->neumann == 1 && blocks_ok && loop_order_ok(a) ? loop_plan(g->nt, g->nz, a.n_cond, g->cus, g->lds_max, lp) : 0;
     const bool loop = loop_rows > 0 && loop_fn(o->precond, loop_rows);
+    g->path = loop ? GAP_PCG_PATH_RESIDENT : GAP_PCG_PATH_LAUNCHES;
     if (loop) {
         const hipError_t fe = hipFuncSetAttribute(loop_fn(o->precond, loop_rows), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                   (int)(kLoopWaves * loop_tile_bytes(loop_rows)));
@@ -2007,6 +2010,13 @@ gap_status gap_kernel_stats(gap_grid_t g, int32_t kernel, int64_t* launches, dou
     if (kernel < 0 || kernel >= GAP_KERNEL_COUNT) return fail(GAP_EINVAL, "unknown kernel %d", kernel);
     if (launches) *launches = g->launches[kernel];
     if (total_ms) *total_ms = g->total_ms[kernel];
+    return GAP_OK;
+}
+
+gap_status gap_pcg_path(gap_grid_t g, int32_t* path)
+{
+    if (!g || !path) return fail(GAP_EINVAL, "grid and path must be non-NULL");
+    *path = g->path;
     return GAP_OK;
 }
 

@@ -35,6 +35,7 @@ GAP_MAX_COND = 9
 GAP_ITERATION_TWO_LAUNCH, GAP_ITERATION_ONE_LAUNCH, GAP_ITERATION_STRIPS = 0, 1, 2
 GAP_KERNEL_PCG_A, GAP_KERNEL_PCG_B, GAP_KERNEL_PCG_ONE, GAP_KERNEL_PCG_STRIPS = 0, 1, 2, 3
 GAP_KERNEL_COUNT = 4
+GAP_PCG_PATH_NONE, GAP_PCG_PATH_LAUNCHES, GAP_PCG_PATH_RESIDENT, GAP_PCG_PATH_GAVE_UP = 0, 1, 2, 3
 KERNEL_NAMES = ["k_pcg_a", "k_pcg_b", "k_pcg_f", "k_pcg_w"]
 
 
@@ -144,6 +145,7 @@ _SIGNATURES = {
     "gap_kernel_stats": [_P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_double)],
     "gap_tune_neumann": [_P, ctypes.POINTER(gap_solver_opts), _P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
                          _D8, _P],
+    "gap_pcg_path": [_P, ctypes.POINTER(ctypes.c_int32)],
     "gap_pcg_history": [_P, ctypes.c_int32],
     "gap_get_pcg_history": [_P, _D8, _D8, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), _P],
 }
@@ -334,6 +336,13 @@ def gap_kernel_stats(handle, kernel):
     ms = ctypes.c_double(0.0)
     _check(load().gap_kernel_stats(handle, int(kernel), ctypes.byref(n), ctypes.byref(ms)))
     return n.value, ms.value
+
+
+def gap_pcg_path(handle):
+    """Which way the last solve of the handle ran (GAP_PCG_PATH_*)."""
+    path = ctypes.c_int32(0)
+    _check(load().gap_pcg_path(handle, ctypes.byref(path)))
+    return path.value
 
 
 def gap_pcg_history(handle, capacity):

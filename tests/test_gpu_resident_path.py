@@ -1,0 +1,80 @@
+"""Which solves run on the resident PCG kernel, by the route the library reports: without it a comparison of the
+resident kernel with the strip kernel passes where both sides ran the same one.  For each resident route the iterate
+is compared with the strip kernel's (plain launches, check_every = 1): 60 iterations, rounding 60 x 1.1e-16 x
+sqrt(kappa) with kappa 3e4, 1.2e-12; tolerance 1e-11."""
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2511_06824_amd import gapsolve as G  # noqa: E402
+from paper_2511_06824_amd.solver import JointGapSolver  # noqa: E402
+
+R, L = G.GAP_PCG_PATH_RESIDENT, G.GAP_PCG_PATH_LAUNCHES
+GLOBAL, PER = G.GAP_SCALARS_GLOBAL, G.GAP_SCALARS_PER_COND
+
+
+def log(msg):
+    print(msg, flush=True)
+
+
+def solver_of(nt, nz, n_cond):
+    case = synth.textured_case(nt, nz, 3)
+    s = JointGapSolver.from_case(case, max_cond=9)
+    s.assemble(case.e, case.edot, case.delta, n_cond)
+    return s
+
+
+@pytest.mark.parametrize("nt,nz,n_cond,path,kw", [
+    (150, 61, 9, R, dict()),
+    (150, 61, 9, R, dict(strategy=G.GAP_STRATEGY_ASYNC)),
+    (150, 61, 9, R, dict(precond=G.GAP_PRECOND_JACOBI)),
+    (150, 61, 9, R, dict(graph=False)),
+    (150, 61, 9, R, dict(graph=False, check_every=4)),
+    (150, 61, 1, R, dict(eps=1e-10)),
+    (150, 61, 1, R, dict(eps=1e-10, scalars=PER, strategy=G.GAP_STRATEGY_ASYNC)),
+    (260, 704, 9, R, dict()),
+    (260, 705, 9, L, dict()),
+    (150, 61, 9, L, dict(graph=False, check_every=3)),
+    (150, 61, 9, L, dict(scalars=PER)),
+    (150, 61, 1, L, dict(eps=1e-8)),
+    (150, 61, 9, L, dict(neumann=2)),
+    (150, 61, 9, L, dict(precond=G.GAP_PRECOND_ASSOR1)),
+    (150, 61, 9, L, dict(iteration=G.GAP_ITERATION_ONE_LAUNCH))])
+def test_route_of_a_solve(nt, nz, n_cond, path, kw):
+    log(f"case: {nt} x {nz} x {n_cond}, {kw}")
+    s = solver_of(nt, nz, n_cond)
+    kw = dict(dict(omega=1.6, eps=1e-10, max_iter=60, raise_on_error=False), **kw)
+    assert G.gap_pcg_path(s.handle) == G.GAP_PCG_PATH_NONE
+    _, i = s.solve(**kw)
+    p = s.pressure().clone()
+    assert G.gap_pcg_path(s.handle) == path
+    if path == R:
+        _, j = s.solve(**dict(kw, graph=False, check_every=1))
+        assert G.gap_pcg_path(s.handle) == L
+        q = s.pressure()
+        assert i.iterations == j.iterations and i.status == j.status
+        assert max(float((a - b).norm() / b.norm()) for a, b in zip(p, q)) <= 1e-11
+    s.close()
+
+
+def test_route_of_the_adjoint_solves():
+    log("case: 150 x 61 x 1, adjoint Jacobian, vector-Jacobian product, base and adjoint systems together")
+    s = solver_of(150, 61, 1)
+    kw = dict(omega=1.6, eps=1e-10)
+    s.solve(**kw)
+    assert G.gap_pcg_path(s.handle) == R
+    s.jacobian_adjoint(w=np.array([1.0, -0.5, 20.0, 30.0]), **kw)      # one system
+    assert G.gap_pcg_path(s.handle) == R
+    s.jacobian_adjoint(**kw)                                            # a recurrence for each of four
+    assert G.gap_pcg_path(s.handle) == L
+    s.solve_with_adjoint(**kw)
+    assert G.gap_pcg_path(s.handle) == L
+    s.close()
