@@ -718,7 +718,7 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
                         sc->iterations = j;
                         sc->rel = rel;
                         sc->status = bad ? -4 : (converged ? 0 : (j >= max_iter ? -3 : 0));
-                        if (stop) sc->done = 1;
+                        sc->done = stop ? 1 : 0;
                         st_out->iter = j + 1;
                         st_out->done = stop ? 1 : 0;
                         st_out->act = (int)active;
@@ -752,13 +752,13 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
         }
         publish_sums(base + (first ? 1u : (unsigned)j + 2u), first);
         if (first) {
-            if (c == 0 && kc == 0 && t == 0) {
+            // A launch has one writer of the record, whose workgroup depends on which condition froze when: here
+            // the launch that forms r_0 alone, otherwise the workgroup above that decides the last pass.
+            if (n_pass == 0 && c == 0 && kc == 0 && t == 0) {
                 sc->done = sc->status = sc->iterations = 0;
-                if (n_pass == 0) {
-                    st_out->iter = 0;
-                    st_out->done = 0;
-                    st_out->act = (int)act;
-                }
+                st_out->iter = 0;
+                st_out->done = 0;
+                st_out->act = (int)act;
             }
         } else {
             ++j;

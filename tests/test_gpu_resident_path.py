@@ -78,3 +78,37 @@ def test_route_of_the_adjoint_solves():
     s.solve_with_adjoint(**kw)
     assert G.gap_pcg_path(s.handle) == L
     s.close()
+
+
+def warm_solver(nt, nz):
+    """A solver, its solution, and a function that starts every condition k from solution * (1 + rel[k])."""
+    s = solver_of(nt, nz, 9)
+    s.solve(omega=1.6, eps=1e-11)
+    exact = s.pressure().clone()
+
+    def start(rel):
+        rel = torch.tensor(rel, dtype=torch.float64, device="cuda:0")
+        s.pressure().copy_(exact * (1.0 + rel.view(9, 1, 1)))
+    return s, exact, start
+
+
+@pytest.mark.parametrize("nt,nz", [(64, 32), (150, 61), (400, 360)])
+@pytest.mark.parametrize("max_iter", [100000, 20])
+def test_record_of_a_solve_whose_first_condition_freezes_first(nt, nz, max_iter):
+    """Another workgroup than that of condition 0 ends the solve: the iterations and status it records stand."""
+    log(f"case: {nt} x {nz} x 9, asynchronous test, condition 0 starts near its solution, at most {max_iter} iterations")
+    s, exact, start = warm_solver(nt, nz)
+    kw = dict(omega=1.6, eps=1e-8, strategy=G.GAP_STRATEGY_ASYNC, warm_start=True, max_iter=max_iter, raise_on_error=False)
+    for k in range(6):
+        rel = [1e-9 if c == 0 else 10.0 ** -((c + k) % 3) for c in range(9)]
+        start(rel)
+        _, j = s.solve(graph=False, check_every=1, **kw)
+        q = s.pressure().clone()
+        for more in (dict(), dict(graph=False, check_every=5)):
+            start(rel)
+            _, i = s.solve(**kw, **more)
+            assert G.gap_pcg_path(s.handle) == R
+            assert i.iterations == j.iterations > 0 and i.status == j.status
+            assert i.status == (G.GAP_OK if max_iter > 20 else G.GAP_ENOCONV)
+            assert max(float((a - b).norm() / b.norm()) for a, b in zip(s.pressure(), q)) <= 1e-9
+    s.close()
