@@ -26,6 +26,8 @@
 // between two buffers by pass parity: a workgroup writes pass e + 2 only after it has seen the
 // sums of pass e + 1 of all others, which they publish after reading pass e.  Every workgroup adds
 // the sums in the same order, so all derive the same alpha, beta and stopping decision to the bit.
+// A condition that the sums of pass e freeze is waited for once more: each of its workgroups publishes empty words of
+// pass e + 1 when it has seen all of pass e, or a late one would find pass e overwritten by the others' pass e + 2.
 // The words of one value lie side by side over the workgroups (a look at 64 of them touches 8 cache
 // lines, not 64: 128 x 64 x 9 4.65 -> 4.25 us per iteration), and a wavefront first waits for the one
 // word of each neighbour: looking at all words from the start fills the fabric and is slower (5.09 us).
@@ -548,6 +550,11 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
         v = lane_sum_16_32(quad_sum(v));
         w = lane_sum_16_32(quad_sum(w));
     };
+    // word t & 1 of this workgroup's value t >> 1 of a pass, threads 0 .. 11
+    auto put_word = [&](unsigned pass_no, double v) {
+        loop_store(lp.words + ((size_t)(pass_no & 1) * 6 + (t >> 1)) * pair_stride + 2 * (c * lp.slots + kc) + (t & 1),
+                   loop_pack(v, t & 1, pass_no));
+    };
     // sums of this workgroup's pass: lanes of each wavefront, then the wavefronts in order
     auto publish_sums = [&](unsigned pass_no, bool first) {
         double x[6], v, w;
@@ -562,8 +569,7 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
         if (t < 12) {
             double s = wsum[0][t >> 1];
             for (int k = 1; k < kLoopWaves; ++k) s += wsum[k][t >> 1];
-            loop_store(lp.words + ((size_t)(pass_no & 1) * 6 + (t >> 1)) * pair_stride + 2 * (c * lp.slots + kc) + (t & 1),
-                       loop_pack(s, t & 1, pass_no));
+            put_word(pass_no, s);
         }
     };
     auto save_p = [&]() {
@@ -594,17 +600,18 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     // ---- iterations ---------------------------------------------------------------------------
     const int n_pass_all = n_pass + (init ? 1 : 0);  // passes at most in this launch
     bool first = init != 0;                          // the next pass forms r_0
+    unsigned heard = act;                            // conditions whose workgroups publish the next pass
     for (int it = 0;; ++it) {
         double alpha = 1.0, beta = 0.0;
         if (!first) {
             const unsigned pass_no = base + (unsigned)j + 1u;   // the pass whose sums are needed
             const int pb = pass_no & 1;
             // The halo as soon as the neighbours have published the pass (a light wait, which leaves the memory to
-            // the last stores), then the slots of all conditions, one a lane (the frozen conditions' are
-            // not waited for).  State in memory is complete at the start of a launch: no halo is
+            // the last stores), then the slots of all conditions, one a lane (those frozen before the last
+            // pass are not waited for).  State in memory is complete at the start of a launch: no halo is
             // needed before its first pass.
             const bool need_halo = it > 0 && has_tile;
-            const bool on = t < n_slots && ((act >> slot_cond) & 1);
+            const bool on = t < n_slots && ((heard >> slot_cond) & 1);
             const loop_word* words = lp.words + (size_t)pb * 6 * pair_stride;
             unsigned my_word = 2 * (on ? t : 0);
             asm volatile("" : "+v"(my_word));        // as j0: no addresses kept across the iterations
@@ -740,9 +747,12 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
                 }
             }
             if (quit) {                              // the solve or this condition (frozen from here on) ends
+                // every wavefront has met the barrier behind its look at the words
+                if (!stop && t < 12) put_word(pass_no + 1u, 0.0);
                 save_p();
                 return;
             }
+            heard = act;
             act = active;
             if (need_halo) halo_keep();
         }
