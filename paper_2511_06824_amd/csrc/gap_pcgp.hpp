@@ -326,11 +326,15 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     };
     auto west = [](double x) { return dpp_shift0<0x138>(x); };
     auto east = [](double x) { return dpp_shift0<0x130>(x); };
+    // r and u of the launch before and for the next one.  Where no launch ends before all its workgroups have read
+    // theirs (two passes or more, each of which waits for the others' sums) one buffer does for both, and
+    // the other keeps the initial guess for the host.
+    auto state = [&](int q) { return n_pass > 1 ? 0 : q & 1; };
     // ---- state of the launch before, or the start: z = p_0, u = 0, r = S, so that the first pass
     // with alpha = 1 and beta = 0 forms r_0 = S - A p_0 and z_0
     {
-        const GAP_AS1 double* rs = as_global((init ? a.S : a.r[j & 1]) + co);
-        const GAP_AS1 double* us = as_global(a.u[j & 1] + co);
+        const GAP_AS1 double* rs = as_global((init ? a.S : a.r[state(j)]) + co);
+        const GAP_AS1 double* us = as_global(a.u[state(j)] + co);
         const GAP_AS1 double* zs = init ? (const GAP_AS1 double*)pp : zbuf(j);
         const bool zz = !init || warm;
         double fs = 0.0;                             // face below
@@ -584,8 +588,8 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     auto save = [&](int q) {
         save_p();
         if (!own) return;
-        GAP_AS1 double* rd = as_global(a.r[q & 1] + co);
-        GAP_AS1 double* ud = as_global(a.u[q & 1] + co);
+        GAP_AS1 double* rd = as_global(a.r[state(q)] + co);
+        GAP_AS1 double* ud = as_global(a.u[state(q)] + co);
         GAP_AS1 double* zd = zbuf(q);
         const int jt = tile_row();
 #pragma unroll

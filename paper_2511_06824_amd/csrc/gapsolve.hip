@@ -383,7 +383,7 @@ hipError_t launch_strip(int Q, int pk, int M, bool sync, bool init, const PcgDev
 // where plain launches were asked for (at least kLoopMinBlock of them, below which a launch per
 // iteration of the strip kernel is faster: 512 x 256 x 9, check_every 1: 41 us against 50).
 constexpr int kLoopPasses = 8192;
-constexpr int kLoopMinBlock = 4;
+constexpr int kLoopMinBlock = 4;                     // two at least: run_loop keeps the initial guess in r[1]
 constexpr size_t kLoopStaticLds = 16384;             // the kernel's own LDS, rounded up
 
 // Tiling of a joint system for the resident kernel: at most one workgroup per CU in all, the
@@ -575,7 +575,6 @@ struct gap_grid_s {
     int* loop_host = nullptr;                                // copy of the abort word, in that of sc_host
     unsigned loop_base = 0;                                  // passes numbered so far
     bool loop_clear = true;                                  // the words hold unknown passes
-    double* loop_p0 = nullptr;                               // warm start: the initial guess, should a launch give up
     int path = GAP_PCG_PATH_NONE;                            // which way the last solve ran
     double *adj_rhs = nullptr, *adj_lam = nullptr;           // adjoint right-hand sides and solutions
     double *adj_part = nullptr;                              // sensitivity partials
@@ -635,7 +634,7 @@ namespace {
 void release(gap_grid_t g)
 {
     double* bufs[] = {g->trig, g->tex, g->kx, g->kz, g->kxz, g->minv, g->S, g->r0, g->r1, g->z, g->z1, g->partial,
-                      g->pcg_part, g->adj_rhs, g->adj_lam, g->adj_part, g->step_buf, g->hist, g->loop_p0};
+                      g->pcg_part, g->adj_rhs, g->adj_lam, g->adj_part, g->step_buf, g->hist};
     for (double* b : bufs)
         if (b) (void)hipFree(b);
     for (auto& gr : g->graphs)
@@ -786,13 +785,8 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
     if (ss != GAP_OK) return ss;
     if (!g->timing) {
         const int passes = o->graph != 0 ? kLoopPasses : check_every;
-        if (a.warm) {
-            if (!g->loop_p0) {
-                gap_status s1 = dmalloc(&g->loop_p0, (size_t)g->max_cond * g->n);
-                if (s1 != GAP_OK) return s1;
-            }
-            HIPCHK(hipMemcpyAsync(g->loop_p0, a.p, p_bytes, hipMemcpyDeviceToDevice, st));
-        }
+        // the initial guess, should a launch give up: in the r and u that launches of two passes or more leave alone
+        if (a.warm) HIPCHK(hipMemcpyAsync(a.r[1], a.p, p_bytes, hipMemcpyDeviceToDevice, st));
         hipError_t e = launch(1, passes, true);
         bool gave_up = e != hipSuccess;
         if (gave_up) (void)hipGetLastError();
@@ -813,7 +807,7 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
         }
         if (!gave_up) return GAP_OK;
         g->path = GAP_PCG_PATH_GAVE_UP;
-        if (a.warm) HIPCHK(hipMemcpyAsync(a.p, g->loop_p0, p_bytes, hipMemcpyDeviceToDevice, st));
+        if (a.warm) HIPCHK(hipMemcpyAsync(a.p, a.r[1], p_bytes, hipMemcpyDeviceToDevice, st));
         ss = start();
         if (ss != GAP_OK) return ss;
     }

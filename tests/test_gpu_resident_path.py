@@ -137,3 +137,20 @@ def test_conditions_that_freeze_one_after_another(nt, nz):
             assert max(float((a - b).norm() / b.norm()) for a, b in zip(p, exact)) <= 1e-5
     assert converged >= 10
     s.close()
+
+
+def test_a_warm_start_allocates_nothing():
+    """The handle holds what gap_grid_bytes says, also after a warm-started solve, on a handle of nine conditions
+    that solves one."""
+    log("case: 512 x 256 x 9 and x 1, device memory across the first warm start")
+    for n_cond in (9, 1):
+        s = solver_of(512, 256, n_cond)
+        kw = dict(omega=1.6, eps=1e-10)
+        s.solve(**kw)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        s.solve(warm_start=True, **kw)
+        assert G.gap_pcg_path(s.handle) == R
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free
+        s.close()
