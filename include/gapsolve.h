@@ -403,10 +403,17 @@ gap_status gap_kernel_stats(gap_grid_t grid, int32_t kernel, int64_t *launches, 
  *   GAP_PCG_PATH_LAUNCHES  launches of the iteration kernel the options name
  *   GAP_PCG_PATH_RESIDENT  the resident kernel (gap_solver_opts, graph)
  *   GAP_PCG_PATH_GAVE_UP   the resident kernel was refused or gave up waiting for workgroups that other
- *                          work kept off the device; the solve was started again without it
+ *                          work kept off the device; the solve was started again on the strip
+ *                          kernel, which the handle's later solves take at once
  * Errors: GAP_EINVAL (NULL argument). */
 enum { GAP_PCG_PATH_NONE = 0, GAP_PCG_PATH_LAUNCHES = 1, GAP_PCG_PATH_RESIDENT = 2, GAP_PCG_PATH_GAVE_UP = 3 };
 gap_status gap_pcg_path(gap_grid_t grid, int32_t *path);
+
+/* The resident kernel's workgroups wait for each other's sums.  seconds (2 unless set): the longest such wait before
+ * the solve is given up and started again on the strip kernel; 0: this handle's solves do not use the resident
+ * kernel.  Also lets a handle try it again that has given it up.  Errors: GAP_EINVAL (NULL grid, negative or
+ * non-finite seconds). */
+gap_status gap_set_resident_wait(gap_grid_t grid, double seconds);
 
 /* Measurement support: record the PCG scalars of every iteration of the following solves of
  * this handle (Table 1 steps 3 and 9): alpha_j and beta_{j-1}, the beta that formed u_j (0 at

@@ -32,11 +32,11 @@
 // lines, not 64: 128 x 64 x 9 4.65 -> 4.25 us per iteration), and a wavefront first waits for the one
 // word of each neighbour: looking at all words from the start fills the fabric and is slower (5.09 us).
 //
-// Every wait is bounded by the clock: a workgroup that waits longer than kLoopWaitTicks sets the
-// abort word and leaves, all others follow, and the host solves again with a launch per pass.
+// Every wait is bounded by the clock: a workgroup that waits longer than wait_ticks sets the
+// abort word and leaves, all others follow, and the host solves again with the strip kernel.
 // The launch is cooperative, so all workgroups are resident.  With n_pass = 1 the same kernel runs
 // one pass from the state that the previous launch left in memory and waits for nothing: that
-// form serves kernel timing and the solve after a wait given up, and gives the same bits.
+// form serves kernel timing, and gives the same bits.
 //
 // Measured per iteration, launches of k_pcg_w and this kernel: 64 x 32 x 1 15.6 and 4.0 us, 128 x 64 x 9
 // 16.2 and 4.1, 256 x 128 x 9 16.9 and 5.0, 512 x 256 x 9 21.8 and 8.6, 400 x 360 x 9 22.9 and 9.3 (18.9, 21.2,
@@ -59,7 +59,8 @@ constexpr int kLoopCols = 64 - 2 * (strip_halo(1) - kLoopHalo);
 constexpr int kLoopWidth = kLoopCols + 1;
 constexpr int kLoopWords = 2 * 6 * 2 * kLoopThreads;    // words of the exchange: two passes, six values, two halves
 constexpr int kLoopSlotsAll = kLoopThreads;          // slots (workgroups) in all, at most: one a thread
-constexpr long long kLoopWaitTicks = 200000000ll;    // 2 s of the 100 MHz clock
+constexpr double kLoopClock = 1e8;                   // ticks of the wall clock per second
+constexpr double kLoopWait = 2.0;                    // seconds a workgroup waits at most, unless the caller sets it
 
 // Where a tile of R rows keeps what it reads every iteration.  r, p and 1/D always stay in registers, u and
 // the conductances where they fit beside them (a SIMD holds one wavefront: 512 registers a lane), z
@@ -82,6 +83,7 @@ struct LoopDev {
     LoopState* state;                                // [2]
     unsigned long long* words;                       // [2][6 values][kLoopSlotsAll][2 halves]
     int* abort_word;
+    long long wait_ticks;
     int slots;                                       // workgroups per condition
     int strips, chunks;                              // tiles per ring and along the axis
 };
@@ -123,17 +125,17 @@ __device__ __forceinline__ double loop_unpack(loop_word lo, loop_word hi)
     return __longlong_as_double((long long)((hi << 32) | (lo & 0xffffffffull)));
 }
 
-// Whether a wait that has looked `spin` times without success is given up.
-__device__ __forceinline__ bool loop_give_up(int spin, long long t0, const int* abort_word)
+// Whether a wait that has looked in vain `spin` times before this one is given up (a limit of 0: at the first look).
+__device__ __forceinline__ bool loop_give_up(int spin, long long t0, const LoopDev& lp)
 {
-    return (spin & 63) == 63 && (wall_clock64() - t0 > kLoopWaitTicks ||
-                                 __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return ((spin & 63) == 63 || lp.wait_ticks == 0) &&
+           (wall_clock64() - t0 >= lp.wait_ticks || __hip_atomic_load(lp.abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
 // Waits until the six pairs of words at p, p + stride, ... of every lane with `on` carry the pass number (each
 // word does, so a load of two need not be atomic), and gives their values (0 elsewhere).  False if the
 // wait was given up.
-__device__ __forceinline__ bool loop_wait_slots(const loop_word* p, size_t stride, bool on, unsigned pass, double (&v)[6], const int* abort_word)
+__device__ __forceinline__ bool loop_wait_slots(const loop_word* p, size_t stride, bool on, unsigned pass, double (&v)[6], const LoopDev& lp)
 {
     typedef unsigned v4u __attribute__((ext_vector_type(4)));
     v4u x0 = {0, 0, 0, 0}, x1 = x0, x2 = x0, x3 = x0, x4 = x0, x5 = x0;
@@ -158,7 +160,7 @@ __device__ __forceinline__ bool loop_wait_slots(const loop_word* p, size_t strid
             ok = here(x0) && here(x1) && here(x2) && here(x3) && here(x4) && here(x5);
         }
         if (__all(ok)) break;
-        given = loop_give_up(spin, t0, abort_word);
+        given = loop_give_up(spin, t0, lp);
         if (given) break;
     }
     auto value = [](v4u x) { return __longlong_as_double((long long)(((loop_word)x.z << 32) | x.x)); };
@@ -171,12 +173,12 @@ __device__ __forceinline__ bool loop_wait_slots(const loop_word* p, size_t strid
     return !given;
 }
 // Waits until the word at p of every lane with `on` carries the pass number.
-__device__ __forceinline__ bool loop_wait_word(const loop_word* p, bool on, unsigned pass, const int* abort_word)
+__device__ __forceinline__ bool loop_wait_word(const loop_word* p, bool on, unsigned pass, const LoopDev& lp)
 {
     const long long t0 = wall_clock64();
     for (int spin = 0;; ++spin) {
         if (__all(!on || (unsigned)(loop_load(p) >> 32) == pass)) return true;
-        if (loop_give_up(spin, t0, abort_word)) return false;
+        if (loop_give_up(spin, t0, lp)) return false;
     }
 }
 
@@ -622,10 +624,10 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
             double x[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             bool ok = true;
             if (need_halo) {
-                ok = loop_wait_word(words + 2 * near_slot, near_on, pass_no, lp.abort_word);
+                ok = loop_wait_word(words + 2 * near_slot, near_on, pass_no, lp);
                 if (ok) halo_load(j);
             }
-            if (ok && wv * 64 < n_slots) ok = loop_wait_slots(words + my_word, pair_stride, on, pass_no, x, lp.abort_word);
+            if (ok && wv * 64 < n_slots) ok = loop_wait_slots(words + my_word, pair_stride, on, pass_no, x, lp);
             if (!ok && lane == 0) gave_up = 1;
 
             // ---- scalars (as in the strip kernel), by every wavefront alike ----------------------

@@ -575,6 +575,8 @@ struct gap_grid_s {
     int* loop_host = nullptr;                                // copy of the abort word, in that of sc_host
     unsigned loop_base = 0;                                  // passes numbered so far
     bool loop_clear = true;                                  // the words hold unknown passes
+    double loop_wait = kLoopWait;                            // seconds its workgroups wait at most; 0: not used
+    bool loop_refused = false;                               // a launch was refused or gave up: solves run without it
     int path = GAP_PCG_PATH_NONE;                            // which way the last solve ran
     double *adj_rhs = nullptr, *adj_lam = nullptr;           // adjoint right-hand sides and solutions
     double *adj_part = nullptr;                              // sensitivity partials
@@ -746,16 +748,17 @@ void fill_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o)
 }
 
 // The resident kernel on a schedule of `blocks` workgroups: a cooperative launch per block of
-// iterations, or, with kernel timing, one launch per iteration of the same kernel.  A cooperative launch that the device refuses, or that gave up waiting for its
-// other workgroups, is replaced by the second form from the start of the solve.
+// iterations, or, with kernel timing, one launch per iteration of the same kernel.  Sets *gave_up, with the initial
+// guess back in place, if the device refused a cooperative launch or its workgroups gave up waiting.
 gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev lp, int rows, const int* work, int blocks,
-                    hipStream_t st)
+                    hipStream_t st, bool* gave_up)
 {
     const int check_every = o->check_every ? o->check_every : 32;
     const size_t p_bytes = (size_t)a.n_cond * g->n * sizeof(double);
     lp.state = g->loop_state;
     lp.abort_word = (int*)(g->loop_state + 2);
     lp.words = (loop_word*)((char*)g->loop_state + kLoopStateBytes);
+    lp.wait_ticks = (long long)(std::min(g->loop_wait, 1e9) * kLoopClock);
     const void* fn = loop_fn(o->precond, rows);
     const PcgDev* reqs = g->req_dev;
     const size_t lds = kLoopWaves * loop_tile_bytes(rows);
@@ -788,28 +791,28 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
         // the initial guess, should a launch give up: in the r and u that launches of two passes or more leave alone
         if (a.warm) HIPCHK(hipMemcpyAsync(a.r[1], a.p, p_bytes, hipMemcpyDeviceToDevice, st));
         hipError_t e = launch(1, passes, true);
-        bool gave_up = e != hipSuccess;
-        if (gave_up) (void)hipGetLastError();
         const long max_blocks = o->max_iter / passes + 2;
-        for (long blk = 0; blk < max_blocks && !gave_up; ++blk) {
-            if (blk) {
-                e = launch(0, passes, true);
-                if (e != hipSuccess) return fail(GAP_EDEVICE, "launch of the resident kernel: %s", hipGetErrorString(e));
+        for (long blk = 0; blk < max_blocks; ++blk) {
+            if (blk) e = launch(0, passes, true);
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                *gave_up = true;
+                break;
             }
             HIPCHK(hipMemcpyAsync(g->sc_host, g->sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, st));
             HIPCHK(hipMemcpyAsync(g->loop_host, lp.abort_word, sizeof(int), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            gave_up = *g->loop_host != 0;
-            if (!gave_up && g->sc_host->done) {
+            if (*g->loop_host != 0) {
+                *gave_up = true;
+                break;
+            }
+            if (g->sc_host->done) {
                 finish();
-                return GAP_OK;
+                break;
             }
         }
-        if (!gave_up) return GAP_OK;
-        g->path = GAP_PCG_PATH_GAVE_UP;
-        if (a.warm) HIPCHK(hipMemcpyAsync(a.p, a.r[1], p_bytes, hipMemcpyDeviceToDevice, st));
-        ss = start();
-        if (ss != GAP_OK) return ss;
+        if (*gave_up && a.warm) HIPCHK(hipMemcpyAsync(a.p, a.r[1], p_bytes, hipMemcpyDeviceToDevice, st));
+        return GAP_OK;
     }
     hipError_t le = launch(1, 0, false);
     if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of the initial residual kernel: %s", hipGetErrorString(le));
@@ -844,6 +847,7 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
 
 gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_t st)
 {
+    const PcgDev asked = a;
     const int check_every = o->check_every ? o->check_every : 32;
     const bool strip = o->iteration == GAP_ITERATION_STRIPS;
     const bool one = o->iteration != GAP_ITERATION_TWO_LAUNCH;
@@ -856,7 +860,8 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     // keeps a launch per iteration: starting and saving the tiles costs a resident launch 20-35 us.
     LoopDev lp{};
     const bool blocks_ok = o->graph != 0 || check_every >= kLoopMinBlock;
-    const int loop_rows = strip && o->neumann == 1 && blocks_ok && loop_order_ok(a) ? loop_plan(g->nt, g->nz, a.n_cond, g->cus, g->lds_max, lp) : 0;
+    const bool loop_ok = strip && o->neumann == 1 && blocks_ok && loop_order_ok(a) && g->loop_wait > 0.0 && !g->loop_refused;
+    const int loop_rows = loop_ok ? loop_plan(g->nt, g->nz, a.n_cond, g->cus, g->lds_max, lp) : 0;
     const bool loop = loop_rows > 0 && loop_fn(o->precond, loop_rows);
     g->path = loop ? GAP_PCG_PATH_RESIDENT : GAP_PCG_PATH_LAUNCHES;
     if (loop) {
@@ -939,7 +944,18 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     *g->req_host = a;
     HIPCHK(hipMemcpyAsync(g->req_dev, g->req_host, sizeof(PcgDev), hipMemcpyHostToDevice, st));
 
-    if (loop) return run_loop(g, a, o, lp, loop_rows, work_b, sch->blocks_b, st);
+    if (loop) {
+        bool gave_up = false;
+        gap_status ls = run_loop(g, a, o, lp, loop_rows, work_b, sch->blocks_b, st, &gave_up);
+        if (!gave_up) return ls;
+        // Other work keeps its workgroups off the device, or the device launches none together: an attempt costs up to
+        // the time they wait, so this handle makes no other.
+        g->loop_refused = true;
+        a = asked;
+        ls = run_pcg(g, a, o, st);
+        g->path = GAP_PCG_PATH_GAVE_UP;
+        return ls;
+    }
     hipError_t le = launch_pcg(sh_b, strip ? kPcgStripInit : (one ? kPcgOneInit : kPcgInit), g->nt, g->req_dev, work_b,
                                sch->blocks_b, st);
     if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of the initial residual kernel: %s", hipGetErrorString(le));
@@ -2004,6 +2020,15 @@ gap_status gap_kernel_stats(gap_grid_t g, int32_t kernel, int64_t* launches, dou
     if (kernel < 0 || kernel >= GAP_KERNEL_COUNT) return fail(GAP_EINVAL, "unknown kernel %d", kernel);
     if (launches) *launches = g->launches[kernel];
     if (total_ms) *total_ms = g->total_ms[kernel];
+    return GAP_OK;
+}
+
+gap_status gap_set_resident_wait(gap_grid_t g, double seconds)
+{
+    if (!g) return fail(GAP_EINVAL, "grid is NULL");
+    if (!is_finite(seconds) || seconds < 0.0) return fail(GAP_EINVAL, "the wait must be finite and >= 0");
+    g->loop_wait = seconds;
+    g->loop_refused = false;
     return GAP_OK;
 }
 

@@ -145,6 +145,7 @@ _SIGNATURES = {
     "gap_kernel_stats": [_P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_double)],
     "gap_tune_neumann": [_P, ctypes.POINTER(gap_solver_opts), _P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
                          _D8, _P],
+    "gap_set_resident_wait": [_P, ctypes.c_double],
     "gap_pcg_path": [_P, ctypes.POINTER(ctypes.c_int32)],
     "gap_pcg_history": [_P, ctypes.c_int32],
     "gap_get_pcg_history": [_P, _D8, _D8, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), _P],
@@ -336,6 +337,12 @@ def gap_kernel_stats(handle, kernel):
     ms = ctypes.c_double(0.0)
     _check(load().gap_kernel_stats(handle, int(kernel), ctypes.byref(n), ctypes.byref(ms)))
     return n.value, ms.value
+
+
+def gap_set_resident_wait(handle, seconds):
+    """Longest wait inside the resident kernel before a solve is given up and run on the strip kernel; 0: the
+    handle does not use the resident kernel."""
+    _check(load().gap_set_resident_wait(handle, float(seconds)))
 
 
 def gap_pcg_path(handle):

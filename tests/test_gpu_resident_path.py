@@ -154,3 +154,37 @@ def test_a_warm_start_allocates_nothing():
         torch.cuda.synchronize()
         assert torch.cuda.mem_get_info()[0] == free
         s.close()
+
+
+@pytest.mark.parametrize("n_cond,kw", [(9, dict()), (9, dict(warm_start=True)), (1, dict(warm_start=True)),
+                                       (9, dict(warm_start=True, graph=False, check_every=5)),
+                                       (9, dict(warm_start=True, strategy=G.GAP_STRATEGY_ASYNC))])
+def test_a_solve_that_gives_the_resident_kernel_up(n_cond, kw):
+    """With no time to wait the first look at words not yet published ends the attempt: the solve starts again from
+    the same guess on the strip kernel, with its bits, and the handle does not try again until told to."""
+    log(f"case: 150 x 61 x {n_cond}, {kw}")
+    s = solver_of(150, 61, n_cond)
+    kw = dict(dict(omega=1.6, eps=1e-9), **kw)
+    s.solve(omega=1.6, eps=1e-3)
+    guess = s.pressure().clone()
+
+    def solve():
+        s.pressure().copy_(guess)
+        _, i = s.solve(**kw)
+        return s.pressure().clone(), i.iterations, G.gap_pcg_path(s.handle)
+
+    G.gap_set_resident_wait(s.handle, 0.0)
+    p, n, path = solve()
+    assert path == L
+    G.gap_set_resident_wait(s.handle, 1e-12)
+    for expected in (G.GAP_PCG_PATH_GAVE_UP, L):
+        q, m, path = solve()
+        assert path == expected and m == n and torch.equal(p, q)
+    G.gap_set_resident_wait(s.handle, 2.0)
+    q, m, path = solve()
+    assert path == R and m == n and float((p - q).norm() / p.norm()) <= 1e-9
+    for bad in (-1.0, float("nan"), float("inf")):
+        with pytest.raises(G.GapError) as ei:
+            G.gap_set_resident_wait(s.handle, bad)
+        assert ei.value.status == G.GAP_EINVAL
+    s.close()
