@@ -385,7 +385,9 @@ gap_status gap_read_system(gap_grid_t grid, int32_t k, double *kx, double *kz, d
  * equally.  k = 0 disables timing; enabling (or re-enabling) resets the counters,
  * disabling keeps them readable.  While enabled the iteration blocks are launched without
  * graph capture (opts->graph is ignored), since events recorded by graph nodes cannot be
- * timed; the results are bitwise the same.
+ * timed; the results are bitwise the same.  A solve on the resident kernel (gap_pcg_path) runs as
+ * without timing, with events around its launches: each of its iterations + 1 passes counts as a
+ * launch of GAP_KERNEL_PCG_STRIPS that takes an equal share of their time.
  * Errors: GAP_EINVAL (NULL grid, k < 0, unknown kernel), GAP_EDEVICE. */
 enum {
     GAP_KERNEL_PCG_A = 0,  /* u = z + beta u; u^T A u; beta and the stopping test (Table 1 steps 9, 3, 6) */

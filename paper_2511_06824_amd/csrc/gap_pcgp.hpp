@@ -34,9 +34,7 @@
 //
 // Every wait is bounded by the clock: a workgroup that waits longer than wait_ticks sets the
 // abort word and leaves, all others follow, and the host solves again with the strip kernel.
-// The launch is cooperative, so all workgroups are resident.  With n_pass = 1 the same kernel runs
-// one pass from the state that the previous launch left in memory and waits for nothing: that
-// form serves kernel timing, and gives the same bits.
+// The launch is cooperative, so all workgroups are resident.
 //
 // Measured per iteration, launches of k_pcg_w and this kernel: 64 x 32 x 1 15.6 and 4.0 us, 128 x 64 x 9
 // 16.2 and 4.1, 256 x 128 x 9 16.9 and 5.0, 512 x 256 x 9 21.8 and 8.6, 400 x 360 x 9 22.9 and 9.3 (18.9, 21.2,
@@ -216,7 +214,7 @@ __device__ __forceinline__ double lane_sum_16_32(double x)
 }
 
 // PK: the preconditioner, 0 Jacobi or 2 ASSOR II.  R: rows of a tile.  init: start a solve with the pass that
-// forms r_0 and z_0.  n_pass: iterations at most in this launch (0: only that first pass).  base:
+// forms r_0 and z_0.  n_pass: iterations at most in this launch, 2 or more.  base:
 // number of the pass before the solve's first.
 template <int PK, int R>
 __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restrict__ reqs, LoopDev lp,
@@ -328,15 +326,12 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     };
     auto west = [](double x) { return dpp_shift0<0x138>(x); };
     auto east = [](double x) { return dpp_shift0<0x130>(x); };
-    // r and u of the launch before and for the next one.  Where no launch ends before all its workgroups have read
-    // theirs (two passes or more, each of which waits for the others' sums) one buffer does for both, and
-    // the other keeps the initial guess for the host.
-    auto state = [&](int q) { return n_pass > 1 ? 0 : q & 1; };
-    // ---- state of the launch before, or the start: z = p_0, u = 0, r = S, so that the first pass
+    // ---- state of the launch before (r and u in the buffers 0: no launch ends before all its workgroups have read
+    // theirs, and the buffers 1 keep the initial guess for the host), or the start: z = p_0, u = 0, r = S, so that the first pass
     // with alpha = 1 and beta = 0 forms r_0 = S - A p_0 and z_0
     {
-        const GAP_AS1 double* rs = as_global((init ? a.S : a.r[state(j)]) + co);
-        const GAP_AS1 double* us = as_global(a.u[state(j)] + co);
+        const GAP_AS1 double* rs = as_global((init ? a.S : a.r[0]) + co);
+        const GAP_AS1 double* us = as_global(a.u[0] + co);
         const GAP_AS1 double* zs = init ? (const GAP_AS1 double*)pp : zbuf(j);
         const bool zz = !init || warm;
         double fs = 0.0;                             // face below
@@ -590,8 +585,8 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     auto save = [&](int q) {
         save_p();
         if (!own) return;
-        GAP_AS1 double* rd = as_global(a.r[state(q)] + co);
-        GAP_AS1 double* ud = as_global(a.u[state(q)] + co);
+        GAP_AS1 double* rd = as_global(a.r[0] + co);
+        GAP_AS1 double* ud = as_global(a.u[0] + co);
         GAP_AS1 double* zd = zbuf(q);
         const int jt = tile_row();
 #pragma unroll
@@ -715,7 +710,8 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
             const bool stop = __builtin_amdgcn_readfirstlane(bad || converged || j >= max_iter) != 0;
             const bool quit = stop || !((active >> c) & 1);
             const bool last = stop || it + 1 == n_pass_all;
-            // the first workgroup of the first condition that was iterating keeps the records
+            // The first workgroup of the first condition that was iterating keeps the records.  Which that is
+            // changes as conditions freeze, so a launch writes the result only here, in its last pass.
             if (kc == 0 && c == __ffs((int)act) - 1 && wv == 0) {
                 // the totals leave out the conditions: lane k adds value q of condition k over its slots
                 auto cond_value = [&](int q) {
@@ -767,18 +763,7 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
             publish_z(first ? 0 : j + 1);
         }
         publish_sums(base + (first ? 1u : (unsigned)j + 2u), first);
-        if (first) {
-            // A launch has one writer of the record, whose workgroup depends on which condition froze when: here
-            // the launch that forms r_0 alone, otherwise the workgroup above that decides the last pass.
-            if (n_pass == 0 && c == 0 && kc == 0 && t == 0) {
-                sc->done = sc->status = sc->iterations = 0;
-                st_out->iter = 0;
-                st_out->done = 0;
-                st_out->act = (int)act;
-            }
-        } else {
-            ++j;
-        }
+        if (!first) ++j;
         first = false;
         if (it + 1 == n_pass_all) {
             save(j);

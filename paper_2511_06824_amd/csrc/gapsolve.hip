@@ -696,6 +696,16 @@ inline void timing_mark(gap_grid_t g, int kind, bool start, hipStream_t st)
     }
 }
 
+// Add `passes` launches of `ms` milliseconds in all, of which one in timing_period counts.
+inline void timing_passes(gap_grid_t g, int kind, int passes, double ms)
+{
+    const long long period = g->timing_period, before = (g->ev_tick + period - 1) / period;
+    g->ev_tick += passes;
+    const long long counted = (g->ev_tick + period - 1) / period - before;
+    g->launches[kind] += counted;
+    g->total_ms[kind] += ms * (double)counted / (double)passes;
+}
+
 // After the stream has been synchronized: add the elapsed times of the recorded pairs.
 gap_status timing_collect(gap_grid_t g)
 {
@@ -748,8 +758,9 @@ void fill_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o)
 }
 
 // The resident kernel on a schedule of `blocks` workgroups: a cooperative launch per block of
-// iterations, or, with kernel timing, one launch per iteration of the same kernel.  Sets *gave_up, with the initial
-// guess back in place, if the device refused a cooperative launch or its workgroups gave up waiting.
+// iterations.  Sets *gave_up, with the initial guess back in place, if the device refused a launch or its workgroups
+// gave up waiting.  Kernel timing takes the events around these launches; a pass counts as a launch of an equal
+// share of their time.
 gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev lp, int rows, const int* work, int blocks,
                     hipStream_t st, bool* gave_up)
 {
@@ -762,86 +773,57 @@ gap_status run_loop(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, LoopDev l
     const void* fn = loop_fn(o->precond, rows);
     const PcgDev* reqs = g->req_dev;
     const size_t lds = kLoopWaves * loop_tile_bytes(rows);
+    const int passes = o->graph != 0 ? kLoopPasses : check_every;
     int par = 0;
-    auto launch = [&](int init, int n_pass, bool coop) -> hipError_t {
-        void* args[] = {(void*)&reqs, (void*)&lp, (void*)&work, (void*)&init, (void*)&n_pass, (void*)&par,
+    auto launch = [&](int init) -> hipError_t {
+        void* args[] = {(void*)&reqs, (void*)&lp, (void*)&work, (void*)&init, (void*)&passes, (void*)&par,
                         (void*)&g->loop_base};
-        const hipError_t e = coop ? hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(kLoopThreads), args, (unsigned)lds, st)
-                                  : hipLaunchKernel(fn, dim3(blocks), dim3(kLoopThreads), args, lds, st);
+        const hipError_t e = hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(kLoopThreads), args, (unsigned)lds, st);
         if (e == hipSuccess) par ^= 1;
         return e;
     };
-    auto start = [&]() -> gap_status {               // number the passes of a solve from here
-        if (g->loop_clear || g->loop_base > 0x60000000u) {
-            HIPCHK(hipMemsetAsync(g->loop_state, 0, kLoopBytes, st));
-            g->loop_base = 0;
-        }
-        g->loop_clear = true;                        // until the solve has ended in order
-        par = 0;
-        return GAP_OK;
-    };
-    auto finish = [&]() {                            // passes the solve has numbered at most
-        g->loop_base += (unsigned)g->sc_host->iterations + 4u;
-        g->loop_clear = false;
-    };
-    gap_status ss = start();
-    if (ss != GAP_OK) return ss;
-    if (!g->timing) {
-        const int passes = o->graph != 0 ? kLoopPasses : check_every;
-        // the initial guess, should a launch give up: in the r and u that launches of two passes or more leave alone
-        if (a.warm) HIPCHK(hipMemcpyAsync(a.r[1], a.p, p_bytes, hipMemcpyDeviceToDevice, st));
-        hipError_t e = launch(1, passes, true);
-        const long max_blocks = o->max_iter / passes + 2;
-        for (long blk = 0; blk < max_blocks; ++blk) {
-            if (blk) e = launch(0, passes, true);
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                *gave_up = true;
-                break;
-            }
-            HIPCHK(hipMemcpyAsync(g->sc_host, g->sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, st));
-            HIPCHK(hipMemcpyAsync(g->loop_host, lp.abort_word, sizeof(int), hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-            if (*g->loop_host != 0) {
-                *gave_up = true;
-                break;
-            }
-            if (g->sc_host->done) {
-                finish();
-                break;
-            }
-        }
-        if (*gave_up && a.warm) HIPCHK(hipMemcpyAsync(a.p, a.r[1], p_bytes, hipMemcpyDeviceToDevice, st));
-        return GAP_OK;
+    // number the passes of this solve from loop_base + 1; until it has ended in order the words are not trusted
+    if (g->loop_clear || g->loop_base > 0x60000000u) {
+        HIPCHK(hipMemsetAsync(g->loop_state, 0, kLoopBytes, st));
+        g->loop_base = 0;
     }
-    hipError_t le = launch(1, 0, false);
-    if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of the initial residual kernel: %s", hipGetErrorString(le));
-    const long max_blocks = o->max_iter / check_every + 2;
-    long enqueued = 0;
+    g->loop_clear = true;
+    if (g->timing) {
+        gap_status ts = timing_reserve(g, 1);
+        if (ts != GAP_OK) return ts;
+    }
+    // the initial guess, should a launch give up: in the r and u that the launches leave alone
+    if (a.warm) HIPCHK(hipMemcpyAsync(a.r[1], a.p, p_bytes, hipMemcpyDeviceToDevice, st));
+    const long max_blocks = o->max_iter / passes + 2;
+    double ms = 0.0;
     for (long blk = 0; blk < max_blocks; ++blk) {
-        const long remaining = (long)o->max_iter - enqueued;
-        const bool last = remaining < check_every;
-        const int iters = last ? (int)remaining : check_every;
-        if (g->timing) {
-            gap_status ts = timing_reserve(g, 2 * iters + 1);
-            if (ts != GAP_OK) return ts;
+        if (g->timing) HIPCHK(hipEventRecord(g->ev[0], st));
+        if (launch(blk == 0) != hipSuccess) {
+            (void)hipGetLastError();
+            *gave_up = true;
+            break;
         }
-        for (int it = 0; it < iters + (last ? 1 : 0); ++it) {   // last: and the closing launch
-            timing_mark(g, GAP_KERNEL_PCG_STRIPS, true, st);
-            le = launch(0, 1, false);
-            timing_mark(g, GAP_KERNEL_PCG_STRIPS, false, st);
-            if (le != hipSuccess) return fail(GAP_EDEVICE, "launch of a PCG iteration: %s", hipGetErrorString(le));
-        }
-        enqueued += iters;
+        if (g->timing) HIPCHK(hipEventRecord(g->ev[1], st));
         HIPCHK(hipMemcpyAsync(g->sc_host, g->sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(g->loop_host, lp.abort_word, sizeof(int), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
-        if (g->timing) {
-            gap_status ts = timing_collect(g);
-            if (ts != GAP_OK) return ts;
+        if (*g->loop_host != 0) {
+            *gave_up = true;
+            break;
         }
-        if (g->sc_host->done) break;
+        if (g->timing) {
+            float t = 0.f;
+            HIPCHK(hipEventElapsedTime(&t, g->ev[0], g->ev[1]));
+            ms += t;
+        }
+        if (g->sc_host->done) {
+            g->loop_base += (unsigned)g->sc_host->iterations + 4u;   // more than the solve has numbered
+            g->loop_clear = false;
+            if (g->timing) timing_passes(g, GAP_KERNEL_PCG_STRIPS, g->sc_host->iterations + 1, ms);
+            break;
+        }
     }
-    if (g->sc_host->done) finish();
+    if (*gave_up && a.warm) HIPCHK(hipMemcpyAsync(a.p, a.r[1], p_bytes, hipMemcpyDeviceToDevice, st));
     return GAP_OK;
 }
 

@@ -188,3 +188,25 @@ def test_a_solve_that_gives_the_resident_kernel_up(n_cond, kw):
             G.gap_set_resident_wait(s.handle, bad)
         assert ei.value.status == G.GAP_EINVAL
     s.close()
+
+
+def test_kernel_timing_measures_the_resident_kernel():
+    """With timing a solve takes the route it takes without, and its passes are faster than strip launches (at this
+    size 8 us against 22)."""
+    log("case: 512 x 256 x 9, kernel timing")
+    s = solver_of(512, 256, 9)
+    kw = dict(omega=1.6, eps=1e-9)
+    average = []
+    for wait in (2.0, 0.0):
+        G.gap_set_resident_wait(s.handle, wait)
+        s.solve(**kw)
+        G.gap_kernel_timing(s.handle, 1)
+        _, i = s.solve(**kw)
+        G.gap_kernel_timing(s.handle, 0)
+        assert G.gap_pcg_path(s.handle) == (R if wait else L)
+        n, ms = G.gap_kernel_stats(s.handle, G.GAP_KERNEL_PCG_STRIPS)
+        assert n == i.iterations + 1 if wait else n > i.iterations
+        average.append(1e3 * ms / n)
+    log(f"  us per pass {average}")
+    assert average[0] < 0.75 * average[1]
+    s.close()
