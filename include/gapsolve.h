@@ -482,7 +482,9 @@ gap_status gap_set_pcg_config(gap_grid_t grid, const gap_pcg_config *cfg);
  * for each kernel of the iteration kind opts->iteration selects (A and B, or F), the fastest
  * configuration (the default unless another is at least 1 % faster), and return the whole
  * configuration in best (may be NULL) with the device time per iteration of the chosen
- * kernels in us (may be NULL).  Overwrites p (caller device memory, n_cond * n
+ * kernels in us (may be NULL).  With GAP_ITERATION_STRIPS that is the strip kernel (W), also for
+ * systems whose solves run on the resident kernel, which has nothing to configure: their strip solves
+ * (a recurrence per condition, adjoint systems) use it.  Overwrites p (caller device memory, n_cond * n
  * doubles) and the handle's Krylov state; call solve_joint_pcg afterwards.  Stream-ordered on
  * stream, synchronizes it; resets the counters of gap_kernel_stats.  Errors: GAP_EINVAL (NULL
  * grid/opts/p, iterations outside [2, 10000]), GAP_ESTATE (nothing assembled), GAP_EDEVICE. */

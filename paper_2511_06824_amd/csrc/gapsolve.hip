@@ -2098,7 +2098,8 @@ gap_status check_shape(gap_grid_t g, PcgShape sh)
 }
 
 // One timed run of the tuner: average device us per launch of A and of B (two-launch
-// iteration), or of the one-launch kernel in *us_a (*us_b = 0).
+// iteration), or of the one-launch kernel in *us_a (*us_b = 0).  The resident kernel has nothing to tune: strips are
+// timed also for systems it would take, for their solves that it does not.
 gap_status tune_run(gap_grid_t g, const gap_solver_opts* t, double* p, void* stream, double* us_a, double* us_b)
 {
     for (int k = 0; k < GAP_KERNEL_COUNT; ++k) {
@@ -2109,7 +2110,10 @@ gap_status tune_run(gap_grid_t g, const gap_solver_opts* t, double* p, void* str
     g->timing = true;
     g->timing_period = 1;
     g->ev_tick = 0;
+    const double wait = g->loop_wait;
+    g->loop_wait = 0.0;
     gap_status s = solve_joint_pcg(g, t, p, nullptr, stream);
+    g->loop_wait = wait;
     g->timing = false;
     g->timing_period = period;
     if (s != GAP_OK && s != GAP_ENOCONV) return s;

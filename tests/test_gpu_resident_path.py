@@ -210,3 +210,24 @@ def test_kernel_timing_measures_the_resident_kernel():
     log(f"  us per pass {average}")
     assert average[0] < 0.75 * average[1]
     s.close()
+
+
+def test_the_tuner_times_the_strip_kernel():
+    """Also where solves run on the resident kernel, which has nothing to tune: the time is that of the strip
+    kernel's launches (22 us at this size; the resident kernel's passes take 8)."""
+    log("case: 512 x 256 x 9, autotuner")
+    s = solver_of(512, 256, 9)
+    kw = dict(omega=1.6, eps=1e-9)
+    cfg, us = s.tune(iterations=40, **kw)
+    assert G.gap_pcg_path(s.handle) == L
+    s.solve(**kw)
+    assert G.gap_pcg_path(s.handle) == R
+    G.gap_set_resident_wait(s.handle, 0.0)
+    s.solve(**kw)
+    G.gap_kernel_timing(s.handle, 1)
+    s.solve(**kw)
+    G.gap_kernel_timing(s.handle, 0)
+    n, ms = G.gap_kernel_stats(s.handle, G.GAP_KERNEL_PCG_STRIPS)
+    log(f"  tuned {cfg['wg_per_cu_w']} workgroups per CU, {us:.1f} us; in a solve {1e3 * ms / n:.1f} us")
+    assert 0.7 < us / (1e3 * ms / n) < 1.4
+    s.close()
