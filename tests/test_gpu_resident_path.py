@@ -231,3 +231,65 @@ def test_the_tuner_times_the_strip_kernel():
     log(f"  tuned {cfg['wg_per_cu_w']} workgroups per CU, {us:.1f} us; in a solve {1e3 * ms / n:.1f} us")
     assert 0.7 < us / (1e3 * ms / n) < 1.4
     s.close()
+
+
+def test_resident_solves_beside_strip_solves_and_a_batch():
+    """Resident solves on one stream while a strip solve that fills the chip and then a batch run on another: they
+    wait for room on the device, do not give up, and have the bits they have alone."""
+    log("case: 512 x 256 x 9 resident, beside 1024 x 512 x 9 strips and a batch of three")
+    import threading
+    s, big = solver_of(512, 256, 9), solver_of(1024, 512, 9)
+    kw = dict(omega=1.6, eps=1e-10)
+    _, i = s.solve(**kw)
+    alone = s.pressure().clone()
+    big.solve(**kw)
+    assert G.gap_pcg_path(big.handle) == L
+    big_alone = big.pressure().clone()
+    torch.cuda.synchronize()
+    done, got, wrong = threading.Event(), [], []
+
+    def strips():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(4):
+                big.solve(**kw)
+                torch.cuda.current_stream().synchronize()
+                if not torch.equal(big.pressure(), big_alone):
+                    wrong.append("strips")
+            members = [solver_of(nt, nz, 9) for nt, nz in ((128, 64), (300, 200), (512, 256))]
+            b = G.gap_batch_create()
+            st = torch.cuda.current_stream().cuda_stream
+            ids = [G.gap_batch_add(b, m.handle, m.options(**kw), m.p.data_ptr(), st) for m in members]
+            left = set(ids)
+            for _ in range(200):
+                G.gap_batch_step(b, 32, True, st)
+                for k in G.gap_batch_poll(b):
+                    G.gap_batch_remove(b, k, st)
+                    left.discard(k)
+                if not left:
+                    break
+            torch.cuda.current_stream().synchronize()
+            d = float((members[2].pressure() - alone).norm() / alone.norm())
+            if not d <= 1e-9:
+                wrong.append(f"batch {d}")
+            G.gap_batch_destroy(b)
+            for m in members:
+                m.close()
+        done.set()
+
+    def resident():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            while not done.is_set() and len(got) < 400:
+                _, k = s.solve(**kw)
+                torch.cuda.current_stream().synchronize()
+                got.append((G.gap_pcg_path(s.handle), k.iterations, torch.equal(s.pressure(), alone)))
+
+    threads = [threading.Thread(target=f) for f in (strips, resident)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    log(f"  {len(got)} resident solves beside the others")
+    assert done.is_set() and not wrong
+    assert got and all(g == (R, i.iterations, True) for g in got)
+    s.close()
+    big.close()
