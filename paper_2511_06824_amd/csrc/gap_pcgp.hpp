@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
             return;
         }
         j = __builtin_amdgcn_readfirstlane(st_in->iter);
-        act = (unsigned)__builtin_amdgcn_readfirstlane(st_in->act);
+        act = (unsigned)__builtin_amdgcn_readfirstlane(st_in->act) & 0xffffu;
         if (!((act >> c) & 1)) return;               // frozen in an earlier launch
         rz_prev = st_in->rz;
         ss_all = st_in->ss;
@@ -601,7 +601,10 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
     // ---- iterations ---------------------------------------------------------------------------
     const int n_pass_all = n_pass + (init ? 1 : 0);  // passes at most in this launch
     bool first = init != 0;                          // the next pass forms r_0
-    unsigned heard = act;                            // conditions whose workgroups publish the next pass
+    // in the upper half of act: the conditions whose workgroups publish the next pass (a register of its own that
+    // lives through the passes costs 2 %: 251 x 97 x 9 5.08 us a pass against 4.98)
+    static_assert(GAP_MAXC <= 16, "two masks of conditions in a word");
+    act |= act << 16;
     for (int it = 0;; ++it) {
         double alpha = 1.0, beta = 0.0;
         if (!first) {
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
             // pass are not waited for).  State in memory is complete at the start of a launch: no halo is
             // needed before its first pass.
             const bool need_halo = it > 0 && has_tile;
-            const bool on = t < n_slots && ((heard >> slot_cond) & 1);
+            const bool on = t < n_slots && ((act >> (16 + slot_cond)) & 1);
             const loop_word* words = lp.words + (size_t)pb * 6 * pair_stride;
             unsigned my_word = 2 * (on ? t : 0);
             asm volatile("" : "+v"(my_word));        // as j0: no addresses kept across the iterations
@@ -675,6 +678,8 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
                 const bool mine = lane < n_cond && ((act >> lane) & 1) && sqrt(s_rr / (s_ss > 0.0 ? s_ss : 1.0)) > eps_mine;
                 active = (unsigned)__builtin_amdgcn_readfirstlane((int)__ballot(mine));
                 all_done = active == 0;
+                // frozen: every wavefront has met the barrier behind its look at the words
+                if (__builtin_expect(!((active >> c) & 1), 0) && t < 12) put_word(pass_no + 1u, 0.0);
                 auto over_conds = [&](double y, bool on) {   // conditions fill at most one row of 16 lanes
                     y = on ? y : 0.0;
                     y += dpp_perm<0x128>(y);
@@ -749,13 +754,10 @@ __global__ __launch_bounds__(kLoopThreads, 1) void k_pcg_p(const PcgDev* __restr
                 }
             }
             if (quit) {                              // the solve or this condition (frozen from here on) ends
-                // every wavefront has met the barrier behind its look at the words
-                if (!stop && t < 12) put_word(pass_no + 1u, 0.0);
                 save_p();
                 return;
             }
-            heard = act;
-            act = active;
+            act = (active & 0xffffu) | (act << 16);
             if (need_halo) halo_keep();
         }
         if (has_tile) {
