@@ -115,10 +115,15 @@ typedef struct {
  *                launches after convergence return at once, so the count is exact
  *   graph        nonzero: each block of check_every iterations is captured once into a
  *                hipGraph and replayed; zero: plain launches.  A system whose vectors fit the
- *                registers and LDS of the chip (about 1.3 million condition-DOFs; Neumann order
- *                1 or Jacobi, GAP_ITERATION_STRIPS) runs its iterations inside one cooperative
- *                launch instead, which the host reads when it ends (graph nonzero), or in one
- *                such launch per check_every iterations (graph zero, check_every >= 4)
+ *                registers and LDS of the chip (256 workgroups of four tiles of 52 x 32 cells, whole
+ *                workgroups per condition: 512 x 256 or 260 x 704 with 9 conditions; Neumann order
+ *                1 or Jacobi, GAP_ITERATION_STRIPS, joint scalars or a single condition with eps <=
+ *                1e-9) runs its iterations inside one cooperative launch instead, which the host
+ *                reads when it ends (graph nonzero), or in one such launch per check_every
+ *                iterations (graph zero, check_every >= 4).  This resident kernel adds in another
+ *                order than the strip kernel: which of the two runs, and with it the last bits of a
+ *                result, follows from these options alone, check_every below 4 and eps among them,
+ *                unless the resident kernel is given up (gap_pcg_path)
  *   iteration    GAP_ITERATION_TWO_LAUNCH: Table 1 as printed, two launches per iteration
  *                (u and u^T A u; then alpha and the updates).  GAP_ITERATION_ONE_LAUNCH:
  *                one launch per iteration, with u^T A u = z^T A z + 2 beta z^T A u_prev +

@@ -29,20 +29,20 @@
 // A condition that the sums of pass e freeze is waited for once more: each of its workgroups publishes empty words of
 // pass e + 1 when it has seen all of pass e, or a late one would find pass e overwritten by the others' pass e + 2.
 // The words of one value lie side by side over the workgroups (a look at 64 of them touches 8 cache
-// lines, not 64: 128 x 64 x 9 4.65 -> 4.25 us per iteration), and a wavefront first waits for the one
-// word of each neighbour: looking at all words from the start fills the fabric and is slower (5.09 us).
+// lines, not 64: 9 % of an iteration of 128 x 64 x 9), and a wavefront first waits for the one
+// word of each neighbour: looking at all words from the start fills the fabric and costs 9 % as well.
 //
 // Every wait is bounded by the clock: a workgroup that waits longer than wait_ticks sets the
 // abort word and leaves, all others follow, and the host solves again with the strip kernel.
 // The launch is cooperative, so all workgroups are resident.
 //
-// Measured per iteration, launches of k_pcg_w and this kernel: 64 x 32 x 1 15.6 and 4.0 us, 128 x 64 x 9
-// 16.2 and 4.1, 256 x 128 x 9 16.9 and 5.0, 512 x 256 x 9 21.8 and 8.6, 400 x 360 x 9 22.9 and 9.3 (18.9, 21.2,
-// 21.6, 29.6 and 30.9 with the launches as they were when this kernel came in).
-// Of the 4.2 us at 128 x 64 the march over 4 rows takes 0.7 (62 instructions a row, issued one each
-// 4 cycles: FP64 rate), the exchange 1.7 (one store to one load across the fabric takes 0.9 at least),
-// the two sums over lanes 0.6, the scalars 0.8 (two dependent divisions); at 512 x 256 the march over
-// 24 rows takes 3.4 of 8.5.
+// Measured per iteration of whole solves, launches of k_pcg_w and this kernel: 64 x 32 x 1 15.8 and 4.2 us, 128 x 64 x 9
+// 16.6 and 4.1, 256 x 128 x 9 17.0 and 4.8, 512 x 256 x 9 21.9 and 8.4, 400 x 360 x 9 23.0 and 9.1.
+// Clocks of one wavefront around the parts of a pass (a build with clock reads, 2.36 GHz), 128 x 64 x 9 and 512 x 256 x 9,
+// us: wait for the neighbours' word 0.9 and 1.2 (one store to one load across the fabric takes 0.9 at
+// least), all words 0.6 and 0.9, sums over lanes 0.5 and 0.7, alpha and beta 0.6 (two dependent divisions), halo 0.2 and
+// 0.3, the march over 4 and 24 rows 0.8 and 3.5 (62 instructions a row, issued one each 4 cycles: FP64
+// rate), boundary cells 0.2 and 0.7, this workgroup's sums and the acknowledgement of its stores 0.5 and 0.7.
 #pragma once
 
 #include <type_traits>

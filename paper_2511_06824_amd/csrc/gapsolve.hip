@@ -380,8 +380,8 @@ hipError_t launch_strip(int Q, int pk, int M, bool sync, bool init, const PcgDev
 
 // ---- resident kernel (gap_pcgp.hpp) ----------------------------------------------------
 // Iterations of one cooperative launch, after which the host reads the record: many, or check_every
-// where plain launches were asked for (at least kLoopMinBlock of them, below which a launch per
-// iteration of the strip kernel is faster: 512 x 256 x 9, check_every 1: 41 us against 50).
+// where plain launches were asked for (at least kLoopMinBlock of them, below which a launch per iteration of the
+// strip kernel is faster: 512 x 256 x 9, check_every 1: 41 us against 50, most of it the tiles' loads and stores).
 constexpr int kLoopPasses = 8192;
 constexpr int kLoopMinBlock = 4;                     // two at least: run_loop keeps the initial guess in r[1]
 constexpr size_t kLoopStaticLds = 16384;             // the kernel's own LDS, rounded up
@@ -390,7 +390,7 @@ constexpr size_t kLoopStaticLds = 16384;             // the kernel's own LDS, ro
 // lowest tiles built that cover the grid so, since the march over a tile (0.1 us a row) is the
 // longest part of an iteration.  The exchange of 252 workgroups takes 0.6 us longer than that of 180,
 // so up to 16 rows a tiling of at most 200 is preferred (256 x 128 x 9: 5.46 us per iteration with 6
-// rows and 252 workgroups, 5.06 with 8 and 180).  Returns the rows, 0 if the system does not fit.
+// rows and 252 workgroups, 4.83 to 5.06 with 8 and 180).  Returns the rows, 0 if the system does not fit.
 int loop_plan(int nt, int nz, int n_cond, int cus, int lds_max, LoopDev& lp)
 {
     int groups = 1;
@@ -410,13 +410,14 @@ int loop_plan(int nt, int nz, int n_cond, int cus, int lds_max, LoopDev& lp)
     return 0;
 }
 
-// Whether a solve may take the resident kernel's order of summation.  A joint recurrence over the
-// conditions is insensitive to it (1e-15 in p at any tolerance).  A recurrence of one condition
+// Whether a solve takes the resident kernel and its order of summation.  A joint recurrence over the
+// conditions is insensitive to the order (1e-15 in p at any tolerance).  A recurrence of one condition
 // is not: where its Ritz values have converged, a change in the last bit of a sum grows until
 // about the residual 1e-6 and shrinks with the residual after it (150 x 61 textured, between any two
-// of the kernels: 3e-9 in p at residual 2e-7, 3e-10 at 9e-9).  A single condition takes this kernel
-// only if it goes on to kLoopTight; several with a recurrence each (forward differences would multiply
-// what is left by 1 / delta) do not.
+// of the kernels: 3e-9 in p at residual 2e-7, 3e-10 at 9e-9).  That is below the error of a solve that stops there; the
+// line is drawn for programs that compare such results.  A single condition takes this kernel if it goes on to
+// kLoopTight, where the kernels agree to 1e-9 and better.  Several with a recurrence each would need an alpha and a beta
+// for each, and k_pcg_p forms one of either.
 constexpr double kLoopTight = 1e-9;
 bool loop_order_ok(const PcgDev& a)
 {
@@ -838,8 +839,8 @@ gap_status run_pcg(gap_grid_t g, PcgDev& a, const gap_solver_opts* o, hipStream_
     fill_pcg(g, a, o);
     a.n_strips = a.strip_groups = 1;
     // Systems whose vectors fit the registers and LDS of the chip run the resident kernel; it needs
-    // Neumann order 1 or Jacobi.  A caller that reads the record after every few plain launches
-    // keeps a launch per iteration: starting and saving the tiles costs a resident launch 20-35 us.
+    // Neumann order 1 or Jacobi.  With few plain launches between two looks at the record a launch per iteration
+    // stays: starting and saving the tiles costs a resident launch 20-35 us.
     LoopDev lp{};
     const bool blocks_ok = o->graph != 0 || check_every >= kLoopMinBlock;
     const bool loop_ok = strip && o->neumann == 1 && blocks_ok && loop_order_ok(a) && g->loop_wait > 0.0 && !g->loop_refused;
